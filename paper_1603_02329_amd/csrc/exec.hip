@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "pat_internal.h"
+#include "solve.h"
 
 namespace pat {
 
@@ -398,6 +399,73 @@ bool eos_init(const pat_plan* p) { return (p->desc.flags & PAT_EOS_INIT) && p->l
 // the initial and final passes a plan needs (plans that share launches must agree)
 int ends_of(const pat_plan* p) { return (smooths_p0(p) ? 1 : 0) | (eos_init(p) ? 2 : 0); }
 
+// ------------------------------------------------------------------ resident solves
+bool timing_on() {
+  std::lock_guard<std::mutex> lk(g_tmu);
+  return g_timing_on;
+}
+bool resident(const pat_plan* p) { return solve_shape(p->desc.ndim, p->hp.n[0], p->hp.n[1]); }
+
+// Whether a batch runs as resident solves: when their estimated time is below
+// that of the batched launches (microseconds, forward, lossy; measured from
+// one to 64 instances of 64^2 to 512^2).  A resident step takes
+// 14 us + 0.28 us per 1000 points on its die, the dies working side by side
+// and each holding 32 / members domains; over every die 30 us + 0.037 us per
+// 1000 points, one instance at a time.  A step of the batched launches takes
+// 42 us + 0.02 us per 1000 points of all its instances.
+bool resident_pays(pat_plan* const* plans, int nb) {
+  double die[kSolveXcds] = {}, whole = 0, longest = 0, work = 0, steps_max = 1;
+  std::vector<double> cost;  // time on a die, by the share of it that the instance holds
+  if (nb > kSolveQueue) return false;
+  for (int i = 0; i < nb; ++i) {
+    const pat_plan* p = plans[i];
+    if (!resident(p)) return false;
+    const int nx = p->hp.n[0], ny = p->hp.n[1];
+    const double steps = std::max(0, p->desc.nt - 1), kpts = 1e-3 * (double)p->npoints;
+    steps_max = std::max(steps_max, steps);
+    work += steps * kpts;
+    if (solve_whole(nx, ny)) {
+      whole += steps * (30.0 + 0.037 * kpts);
+    } else {
+      const double t = steps * (14.0 + 0.28 * kpts);
+      longest = std::max(longest, t);
+      cost.push_back(t * solve_members(nx, ny) / kSolveCus);
+    }
+  }
+  std::sort(cost.rbegin(), cost.rend());
+  for (double c : cost) *std::min_element(die, die + kSolveXcds) += c;
+  const double t_res = whole + std::max(longest, *std::max_element(die, die + kSolveXcds));
+  return t_res < steps_max * 42.0 + 0.02 * work;
+}
+
+SolveArgs solve_args(void* ctl, int domains) {
+  SolveArgs a{};
+  a.ctl = (SolveCtl*)ctl;
+  a.doms = (SolveDom*)((char*)ctl + sizeof(SolveCtl));
+  a.domains = domains;
+  a.s0 = 0;
+  a.s1 = -1;
+  return a;
+}
+
+// steps [s0, s1) of one plan in one launch
+int solve_one(const pat_plan* p, int dir, int s0, int s1, hipStream_t st) {
+  if (s1 <= s0) return PAT_OK;
+  SolveArgs a = solve_args(p->solve, 1);
+  a.one = p->dp;
+  for (int x = 1; x <= kSolveXcds; ++x) a.first[x] = 1;  // whichever die's domain asks first runs it
+  a.members = solve_members(p->hp.n[0], p->hp.n[1]);
+  a.s0 = s0;
+  a.s1 = s1;
+  return launch_solve(p->hp.n[0], p->hp.n[1], dir, p->lossy, a, st) == hipSuccess ? PAT_OK : PAT_EHIP;
+}
+
+// the time loop of one plan: steps [s0, s1) of direction dir
+int run_one(const pat_plan* p, const Runner& R, int dir, int s0, int s1, hipStream_t st) {
+  if (dir < 2 && resident(p) && !timing_on()) return solve_one(p, dir, s0, s1, st);
+  return R.steps(dir, s0, s1, st);
+}
+
 }  // namespace
 }  // namespace pat
 
@@ -410,7 +478,7 @@ extern "C" int pat_forward(pat_plan* p, const float* p0, float* data, void* stre
   const Runner R = eager_runner(p);
   int rc = set_io(p, p0, data, st);
   if (!rc) rc = R.init(smooths_p0(p), eos_init(p), st);
-  if (!rc) rc = R.steps(0, 0, p->desc.nt - 1, st);
+  if (!rc) rc = run_one(p, R, 0, 0, p->desc.nt - 1, st);
   if (!rc) rc = R.reduce(0, 0, st, reduce_blocks(p->desc.nt, p->desc.n_sensors));
   return rc;
 }
@@ -425,7 +493,7 @@ extern "C" int pat_adjoint(pat_plan* p, const float* data, float* img, void* str
     rc = R.row(R_ADJ_SCATTER_ONLY, StepArg{nullptr, 0}, st);
   } else {
     rc = scatter_sums(p->dp, 1, (long)p->desc.nt * p->hp.ngroups, st);
-    if (!rc) rc = R.steps(1, 0, p->desc.nt - 1, st);
+    if (!rc) rc = run_one(p, R, 1, 0, p->desc.nt - 1, st);
     if (!rc) rc = R.adj_final(eos_init(p), st);
   }
   if (!rc) rc = R.smooth_out(smooths_p0(p), st);
@@ -468,7 +536,7 @@ extern "C" int pat_forward_range(pat_plan* p, const float* p0, float* data, int3
     s0 = n_begin - 1;
   }
   // step n records sample n + 1: samples n_begin..n_end-1 need steps s0..n_end-2
-  if (!rc) rc = R.steps(0, s0, n_end - 1, st);
+  if (!rc) rc = run_one(p, R, 0, s0, n_end - 1, st);
   if (!rc) rc = R.reduce(n_begin, n_end, st, reduce_blocks(n_end - n_begin, p->desc.n_sensors));
   if (!rc && hipMemcpyAsync(state_io, state, p->state_bytes, hipMemcpyDeviceToDevice, st) != hipSuccess)
     rc = PAT_EHIP;
@@ -599,6 +667,18 @@ struct pat_batch {
   hipEvent_t lead = nullptr;  // the first group's first pass (staggered start)
   bool stagger = true;
   int nb = 0;
+  // resident solves: per shape and physics the queue of the instances with a
+  // time loop, the dies' lists one after another
+  struct Queue {
+    int nx = 0, ny = 0, lossy = 0;
+    std::vector<std::pair<int, int>> order[kSolveXcds];  // (class, instance)
+    const DevPlan** list = nullptr;
+    void* ctl = nullptr;
+    int first[kSolveXcds + 1] = {};
+    int members = 0, domains = 0;
+  };
+  bool resident = false;
+  std::vector<Queue> queue;
 };
 
 namespace {
@@ -707,7 +787,7 @@ int run_steps(pat_batch* b, BatchClass& c, int dir, int nsteps, hipEvent_t lead 
   return rc;
 }
 
-int set_io_class(BatchClass& c, const float* const* in, float* const* out) {
+int set_io_class(BatchClass& c, const float* const* in, float* const* out, hipStream_t st) {
   for (size_t i0 = 0; i0 < c.plans.size(); i0 += kIoMax) {
     IoArgs a{};
     const int n = (int)std::min<size_t>(kIoMax, c.plans.size() - i0);
@@ -717,8 +797,55 @@ int set_io_class(BatchClass& c, const float* const* in, float* const* out) {
       a.in[i] = in[k];
       a.out[i] = out[k];
     }
-    hipLaunchKernelGGL(k_set_io_many, dim3(1), dim3(kIoMax), 0, c.st, c.recs + i0, n, a);
+    hipLaunchKernelGGL(k_set_io_many, dim3(1), dim3(kIoMax), 0, st, c.recs + i0, n, a);
     if (hipGetLastError() != hipSuccess) return PAT_EHIP;
+  }
+  return PAT_OK;
+}
+
+// Resident solves of every instance: the initial passes of each group, one
+// launch per physics for all time loops, the final passes.
+int batch_run_resident(pat_batch* b, int dir, const float* const* in, float* const* out, hipStream_t st) {
+  int rc = PAT_OK;
+  for (auto& c : b->cls) {
+    rc = set_io_class(c, in, out, st);
+    const Runner R = c.runner();
+    if (!rc && dir == 0) {
+      rc = R.init(c.smooth_p0, c.eos, st);
+    } else if (!rc && c.nt > 1) {
+      long most = 0;
+      for (auto* pl : c.plans) most = std::max(most, (long)pl->desc.nt * pl->hp.ngroups);
+      rc = scatter_sums(c.recs, (int)c.plans.size(), most, st);
+    }
+    if (rc) return rc;
+  }
+  // the queues run side by side: the first on the caller's stream, the
+  // others on lanes forked from it and joined again
+  const size_t nq = b->queue.size();
+  if (nq > 1 && hipEventRecord(b->fork, st) != hipSuccess) return PAT_EHIP;
+  for (size_t k = 0; k < nq; ++k) {
+    const auto& q = b->queue[k];
+    SolveArgs a = solve_args(q.ctl, q.domains);
+    a.list = q.list;
+    a.members = q.members;
+    for (int x = 0; x <= kSolveXcds; ++x) a.first[x] = q.first[x];
+    hipStream_t s = k == 0 ? st : b->lanes[(k - 1) % b->lanes.size()];
+    if (k > 0 && hipStreamWaitEvent(s, b->fork, 0) != hipSuccess) return PAT_EHIP;
+    if (launch_solve(q.nx, q.ny, dir, q.lossy, a, s) != hipSuccess) return PAT_EHIP;
+  }
+  for (size_t k = 0; nq > 1 && k < std::min(nq - 1, b->lanes.size()); ++k) {
+    if (hipEventRecord(b->lead, b->lanes[k]) != hipSuccess || hipStreamWaitEvent(st, b->lead, 0) != hipSuccess)
+      return PAT_EHIP;
+  }
+  for (auto& c : b->cls) {
+    const Runner R = c.runner();
+    if (dir == 0) {
+      rc = R.reduce(0, 0, st, c.red_n);
+    } else {
+      rc = c.nt == 1 ? R.row(R_ADJ_SCATTER_ONLY, StepArg{nullptr, 0}, st) : R.adj_final(c.eos, st);
+      if (!rc) rc = R.smooth_out(c.smooth_p0, st);
+    }
+    if (rc) return rc;
   }
   return PAT_OK;
 }
@@ -729,13 +856,14 @@ int set_io_class(BatchClass& c, const float* const* in, float* const* out) {
 // another's row pass (memory-bound) rather than two of a kind.
 int batch_run(pat_batch* b, int dir, const float* const* in, float* const* out, hipStream_t st) {
   if (!b || !in || !out) return PAT_EINVAL;
+  if (b->resident && !timing_on()) return batch_run_resident(b, dir, in, out, st);
   if (hipEventRecord(b->fork, st) != hipSuccess) return PAT_EHIP;
   const bool stagger = b->stagger && b->cls.size() > 1;
   int rc = PAT_OK;
   for (size_t k = 0; k < b->cls.size(); ++k) {
     BatchClass& c = b->cls[k];
     if (hipStreamWaitEvent(c.st, b->fork, 0) != hipSuccess) return PAT_EHIP;
-    rc = set_io_class(c, in, out);
+    rc = set_io_class(c, in, out, c.st);
     if (rc) return rc;
     const Runner R = c.runner();
     hipEvent_t lead = (stagger && k == 0) ? b->lead : nullptr;
@@ -992,6 +1120,46 @@ extern "C" int pat_batch_create_ex(pat_batch** out, pat_plan* const* plans, int3
     l.ctr = take(sizeof(int32_t));
     lay.push_back(l);
   }
+  // resident solves: the instances of each shape and physics, longest first,
+  // go to the die with the least work so far
+  b->resident = resident_pays(plans, nb);
+  std::vector<size_t> off_list, off_ctl;
+  if (b->resident) {
+    struct Work {
+      double w;
+      int k, i;
+    };
+    std::map<std::tuple<int, int, int>, std::vector<Work>> shapes;
+    for (size_t k = 0; k < b->cls.size(); ++k)
+      for (size_t i = 0; i < b->cls[k].plans.size(); ++i) {
+        const pat_plan* p = b->cls[k].plans[i];
+        if (p->desc.nt < 2) continue;
+        shapes[std::make_tuple(p->hp.n[0], p->hp.n[1], p->lossy)].push_back(
+            Work{(double)p->npoints * (p->desc.nt - 1), (int)k, (int)i});
+      }
+    double load[kSolveXcds] = {};
+    for (auto& sh : shapes) {
+      auto& work = sh.second;
+      std::stable_sort(work.begin(), work.end(), [](const Work& x, const Work& y) { return x.w > y.w; });
+      b->queue.emplace_back();
+      auto& q = b->queue.back();
+      std::tie(q.nx, q.ny, q.lossy) = sh.first;
+      for (const auto& w : work) {
+        const int x = (int)(std::min_element(load, load + kSolveXcds) - load);
+        q.order[x].emplace_back(w.k, w.i);
+        load[x] += w.w;
+      }
+      int deep = 1;
+      for (int x = 0; x < kSolveXcds; ++x) {
+        q.first[x + 1] = q.first[x] + (int)q.order[x].size();
+        deep = std::max(deep, (int)q.order[x].size());
+      }
+      q.members = solve_members(q.nx, q.ny);
+      q.domains = solve_whole(q.nx, q.ny) ? 1 : std::max(1, std::min({deep, kSolveDomains, kSolveCus / q.members}));
+      off_list.push_back(take(sizeof(DevPlan*) * work.size()));
+      off_ctl.push_back(take(solve_ctl_bytes(q.domains)));
+    }
+  }
   int rc = PAT_OK;
   if (hipMalloc(&b->arena, off) != hipSuccess) {
     delete b;
@@ -1017,6 +1185,16 @@ extern "C" int pat_batch_create_ex(pat_batch** out, pat_plan* const* plans, int3
         rc = PAT_EHIP;
     }
     if (!rc && hipEventCreateWithFlags(&c.done, hipEventDisableTiming) != hipSuccess) rc = PAT_EHIP;
+  }
+  for (size_t k = 0; k < b->queue.size() && !rc; ++k) {
+    auto& q = b->queue[k];
+    std::vector<const DevPlan*> list;
+    for (const auto& die : q.order)
+      for (const auto& ki : die) list.push_back(b->cls[ki.first].recs + ki.second);
+    q.list = (const DevPlan**)(A + off_list[k]);
+    q.ctl = A + off_ctl[k];
+    if (hipMemcpy(q.list, list.data(), sizeof(DevPlan*) * list.size(), hipMemcpyHostToDevice) != hipSuccess)
+      rc = PAT_EHIP;
   }
   // Streams: by default one per group.  With fewer streams than groups, the
   // groups go heaviest first (grid points x steps) to the least-loaded

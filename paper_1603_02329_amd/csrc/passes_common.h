@@ -36,6 +36,34 @@ __device__ __forceinline__ void gst(T* p, long i, T v) {
   p[i] = v;
 #endif
 }
+// 64-bit accesses at agent scope (relaxed): past the vector L1, seen by and
+// seeing what another compute unit exchanges within the same launch.
+__device__ __forceinline__ float2 gld_agent(const float2* p, long i) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  union {
+    unsigned long long u;
+    float2 f;
+  } c;
+  c.u = __hip_atomic_load((const __attribute__((address_space(1))) unsigned long long*)(p + i), __ATOMIC_RELAXED,
+                          __HIP_MEMORY_SCOPE_AGENT);
+  return c.f;
+#else
+  return p[i];
+#endif
+}
+__device__ __forceinline__ void gst_agent(float2* p, long i, float2 v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  union {
+    unsigned long long u;
+    float2 f;
+  } c;
+  c.f = v;
+  __hip_atomic_store((__attribute__((address_space(1))) unsigned long long*)(p + i), c.u, __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_AGENT);
+#else
+  p[i] = v;
+#endif
+}
 __device__ __forceinline__ float2 ld2(const float* a, long i) { return gld(reinterpret_cast<const float2*>(a), i); }
 __device__ __forceinline__ void st2(float* a, long i, float2 v) { gst(reinterpret_cast<float2*>(a), i, v); }
 __device__ __forceinline__ float2 f2(float a, float b) { return make_float2(a, b); }

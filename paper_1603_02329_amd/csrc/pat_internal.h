@@ -254,4 +254,5 @@ struct pat_plan {
   void* arena = nullptr;        // all device buffers of the plan
   size_t arena_bytes = 0;
   size_t state_bytes = 0;
+  void* solve = nullptr;        // control block of the resident solve (solve.h), one domain per die
 };

@@ -23,11 +23,13 @@
 
 #include "host_plan.h"
 #include "pat_internal.h"
+#include "solve.h"
 
 namespace pat {
 hipError_t upload_twiddles_rows(const Tw* host);
 hipError_t upload_twiddles_cols(const Tw* host);
 hipError_t upload_twiddles_fused(const Tw* host);
+hipError_t upload_twiddles_solve(const Tw* host);
 }
 
 using namespace pat;
@@ -58,7 +60,7 @@ int ensure_twiddles() {
     tw[q] = Tw{ch, sh, (float)(c - (double)ch), (float)(s - (double)sh)};
   }
   if (upload_twiddles_rows(tw.data()) != hipSuccess || upload_twiddles_cols(tw.data()) != hipSuccess ||
-      upload_twiddles_fused(tw.data()) != hipSuccess)
+      upload_twiddles_fused(tw.data()) != hipSuccess || upload_twiddles_solve(tw.data()) != hipSuccess)
     return PAT_EHIP;
   g_tw_ready[dev] = 1;
   return PAT_OK;
@@ -168,6 +170,7 @@ extern "C" int pat_plan_create(pat_plan** out, const pat_desc* desc, const float
   const size_t o_part = cv.take<float>((size_t)d.nt * so.nslots);
   const size_t o_bad = cv.take<int32_t>(1);
   const size_t o_rec = cv.take<DevPlan>(1);
+  const size_t o_solve = cv.take<char>(solve_ctl_bytes(1));
   p->arena_bytes = (cv.off + 255) & ~size_t(255);
   p->state_bytes = state_end - state_begin;
   if (hipMalloc(&p->arena, p->arena_bytes) != hipSuccess) {
@@ -320,6 +323,7 @@ extern "C" int pat_plan_create(pat_plan** out, const pat_desc* desc, const float
   h.partial = (float*)(A + o_part);
   h.bad = (int32_t*)(A + o_bad);
   p->dp = (DevPlan*)(A + o_rec);
+  p->solve = A + o_solve;
   if (!rc) rc = up(o_rec, &h, sizeof(DevPlan));
   if (!rc && hipStreamSynchronize(st) != hipSuccess) rc = PAT_EHIP;
   if (rc) {
@@ -359,7 +363,7 @@ extern "C" int pat_plan_sync(pat_plan* p, void* stream) {
   if (hipMemcpy(&bad, p->hp.bad, 4, hipMemcpyDeviceToHost) != hipSuccess) return PAT_EHIP;
   if (bad) {
     if (hipMemset(p->hp.bad, 0, 4) != hipSuccess) return PAT_EHIP;
-    return PAT_ENONFINITE;
+    return (bad & 2) ? PAT_EHIP : PAT_ENONFINITE;  // 2: a resident solve gave up waiting
   }
   return PAT_OK;
 }

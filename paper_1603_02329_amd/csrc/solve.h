@@ -1,0 +1,77 @@
+// Resident solves, host and device declarations (passes_solve.h).
+#pragma once
+
+#include "pat_internal.h"
+
+namespace pat {
+
+constexpr int kSolveXcds = 8;        // MI355X: 8 accelerator complex dies (XCDs), one L2 each
+constexpr int kSolveCus = 32;        // compute units per die
+constexpr int kSolveDomains = 16;    // most domains per die
+constexpr int kSolveQueue = 32768;   // most instances of a queue (16 bits hold a claim)
+constexpr int kSolveSpin = 1 << 24;  // polls after which a wait gives up (seconds)
+constexpr uint32_t kSolveClosed = 0x80000000u;
+constexpr uint64_t kSolveRollTicks = 10000;  // of the 100 MHz clock
+
+// Grids above this run on one domain over every die, the others on one die.
+// Per step (forward, lossy), on one die and over all: 256^2 27.8 and 30.6 us;
+// 512 x 128 27.0 and 29.5; 512 x 256 50.2 and 31.5; 512^2 87.6 and 39.5.
+constexpr int kSolveDiePoints = 65536;
+constexpr bool solve_whole(int nx, int ny) { return nx * ny > kSolveDiePoints; }
+// Rows and columns are carried by two lanes where the per-launch passes have
+// one (PairStage): 4 values per lane; 8 for columns of 512 points, which would
+// not fit one wavefront otherwise.
+constexpr bool solve_pair_col(int ny) { return ny <= 256; }
+// rows of nx points that one wavefront carries
+constexpr int solve_rows(int nx) { return 512 / nx; }
+// wavefronts that a row pass of both parts can use
+constexpr int solve_waves(int nx, int ny) { return 2 * (ny / solve_rows(nx)); }
+// compute units of a domain
+constexpr int solve_cus(int nx, int ny) { return kSolveCus * (solve_whole(nx, ny) ? kSolveXcds : 1); }
+// wavefronts per member: two at least (the two parts of a tile exchange
+// through LDS), more once the tiles fill every compute unit
+constexpr int solve_nw(int nx, int ny) {
+  int nw = 2;
+  while (nw < 8 && nw * solve_cus(nx, ny) < solve_waves(nx, ny)) nw *= 2;
+  return nw;
+}
+// members the tiles keep busy, at most one per compute unit
+constexpr int solve_members(int nx, int ny) {
+  const int m = solve_waves(nx, ny) / solve_nw(nx, ny), cap = solve_cus(nx, ny);
+  return m < 1 ? 1 : m < cap ? m : cap;
+}
+
+// One domain: its roll, the instance its first member claimed, and the
+// barrier words: a flag per member, die by die, and one word per die.
+struct alignas(128) SolveDom {
+  uint32_t roll, n, claim, ready;
+  uint32_t count[kSolveXcds];  // members per die (domains over every die)
+  alignas(128) uint32_t lead[kSolveXcds];
+  alignas(128) uint32_t flag[kSolveXcds * kSolveCus];
+};
+struct alignas(128) SolveCtl {
+  uint32_t ticket[kSolveXcds][32];  // blocks seen per die
+  uint32_t head[kSolveXcds][32];    // next instance of each die's list
+};
+
+struct SolveArgs {
+  const DevPlan* const* list;  // queued instances, the dies' lists one after another
+  const DevPlan* one;          // the instance when there is no list
+  const Tw* tw;                // the global twiddle table
+  SolveCtl* ctl;
+  SolveDom* doms;              // [die][domains]; domains over every die: one
+  int32_t first[kSolveXcds + 1];  // where each die's list begins
+  int32_t members, domains;    // members per domain, domains per die
+  int32_t s0, s1;
+};
+
+constexpr size_t solve_ctl_bytes(int domains) { return sizeof(SolveCtl) + sizeof(SolveDom) * kSolveXcds * domains; }
+
+// whether there is a resident kernel for the grid
+inline bool solve_shape(int ndim, int nx, int ny) {
+  return ndim == 2 && nx >= 32 && nx <= 512 && ny >= 32 && ny <= 512;
+}
+// clears the control block and runs the queue's time loops, all of one shape
+hipError_t launch_solve(int nx, int ny, int dir, int lossy, SolveArgs a, hipStream_t st);
+
+}  // namespace pat
