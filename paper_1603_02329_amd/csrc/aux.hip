@@ -145,6 +145,141 @@ __global__ void k_prox_zero_b(ProxBatch b) {  // r and p_prev of every image
   for (int a = 0; a < 2 * b.ndim; ++a) b.r[k][(long)a * g.N + i] = 0.f;
 }
 
+// ------------------------------------------------------------------ FGP prox, 2D, several iterations per launch
+// A workgroup carries a window of the image through k iterations and keeps
+// what they changed in its interior: lane = column, kProxRows rows of each
+// wavefront, z, the dual iterate and p_prev in registers.  Neighbours along x
+// come from the next lane, along y from the same wavefront or, at its first
+// and last row, through LDS.  An iteration spoils one more row and column on
+// each side of the window (and the last primal step one on the low sides),
+// so a launch of k iterations keeps 64 - 2 k columns and kProxH - 2 k rows.
+//
+// Two launches an iteration (the kernels above) are bound by the launches up
+// to 512^2, 4.2 us each; here the arithmetic bounds it (square root, two
+// divisions, 1.5 us per iteration).  20 iterations, before and after: 64^2
+// 135 and 30 us, 512^2 175 and 35, 1024^2 372 and 95; 16 of 512^2 with 16 of
+// 256^2 2.01 and 0.46 ms.  Rows per wavefront at 512^2, 1024^2: two 45, 121
+// us, three 35, 95, four 42, 99.
+constexpr int kProxWaves = 16, kProxRows = 3, kProxH = kProxWaves * kProxRows;
+
+struct ProxImage {
+  int n0, n1;
+  const float* z;
+  const float* lower;
+  float* x;
+  float* r;  // dual iterate (2 N), then p_prev (2 N)
+  float lam, step;
+};
+struct ProxSteps {
+  int k;       // iterations of this launch
+  int first;   // starts from r = p_prev = 0; otherwise they are read from the workspace
+  int last;    // ends in x; otherwise r and p_prev go to the workspace
+  int tx, ty;  // columns and rows kept
+  float theta[kProxH / 2];
+};
+
+// the value of the lane before (after) this one; 0 past the wavefront's end
+__device__ __forceinline__ float lane_before(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float lane_after(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xf, 0xf, true));
+}
+
+__device__ __forceinline__ void prox_window(const ProxImage& g, const ProxSteps& s, int tile) {
+  __shared__ float row_r[kProxWaves + 1][64], row_x[kProxWaves + 1][64];
+  const int lane = (int)threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int tiles_x = (g.n0 + s.tx - 1) / s.tx, tile_y = tile / tiles_x, tile_x = tile - tile_y * tiles_x;
+  const int lo = s.k + s.last;  // rows and columns before the kept ones
+  const int gx = tile_x * s.tx - lo + lane, gy0 = tile_y * s.ty - lo + wave * kProxRows;
+  const long N = (long)g.n0 * g.n1;
+  const bool in_x = gx >= 0 && gx < g.n0, diff_x = gx >= 0 && gx < g.n0 - 1;
+  float z[kProxRows], low[kProxRows], r0[kProxRows], r1[kProxRows], p0[kProxRows], p1[kProxRows], x[kProxRows];
+#pragma unroll
+  for (int m = 0; m < kProxRows; ++m) {
+    const int gy = gy0 + m;
+    const bool in = in_x && gy >= 0 && gy < g.n1;
+    const long i = in ? (long)gy * g.n0 + gx : 0;
+    z[m] = in ? g.z[i] : 0.f;
+    low[m] = in && g.lower ? g.lower[i] : 0.f;
+    r0[m] = r1[m] = p0[m] = p1[m] = 0.f;
+    if (!s.first && in) {
+      r0[m] = g.r[i];
+      r1[m] = g.r[N + i];
+      p0[m] = g.r[2 * N + i];
+      p1[m] = g.r[3 * N + i];
+    }
+  }
+  if (wave == 0) row_r[0][lane] = 0.f;
+  if (wave == kProxWaves - 1) row_x[kProxWaves][lane] = 0.f;
+  // x = max(z - lam L a, lower), the last row's a_1 of the wavefront before in `up`
+  auto primal = [&](const float* a0, const float* a1, float up) {
+#pragma unroll
+    for (int m = 0; m < kProxRows; ++m) {
+      const float left = lane_before(a0[m]);
+      const float div = ((a0[m] - left) + a1[m]) - (m ? a1[m - 1] : up);
+      x[m] = fmaxf(fmaf(-g.lam, div, z[m]), low[m]);
+    }
+  };
+  const int row0 = wave * kProxRows;
+  const bool in_y = gy0 + kProxRows > 0 && gy0 < g.n1;
+  for (int it = 0; it < s.k; ++it) {
+    // a wavefront whose rows are spoilt, or outside the image, is done with them
+    const bool use = in_y && row0 + kProxRows > it && row0 < kProxH - it;
+    row_r[wave + 1][lane] = r1[kProxRows - 1];
+    __syncthreads();
+    if (use) {
+      primal(r0, r1, row_r[wave][lane]);
+      row_x[wave][lane] = x[0];
+    }
+    __syncthreads();
+    if (!use) continue;
+    const float down = row_x[wave + 1][lane];
+    const float theta = s.theta[it];
+#pragma unroll
+    for (int m = 0; m < kProxRows; ++m) {
+      const int gy = gy0 + m;
+      const float right = lane_after(x[m]), below = m + 1 < kProxRows ? x[m + 1] : down;
+      const float v0 = fmaf(g.step, diff_x ? x[m] - right : 0.f, r0[m]);
+      const float v1 = fmaf(g.step, gy >= 0 && gy < g.n1 - 1 ? x[m] - below : 0.f, r1[m]);
+      const float len = fmaxf(1.f, sqrtf(fmaf(v1, v1, v0 * v0)));
+      const float q0 = v0 / len, q1 = v1 / len;
+      r0[m] = fmaf(theta, q0 - p0[m], q0);
+      r1[m] = fmaf(theta, q1 - p1[m], q1);
+      p0[m] = q0;
+      p1[m] = q1;
+    }
+  }
+  if (s.last) {  // x of the last dual point itself, not of the extrapolated one
+    row_r[wave + 1][lane] = p1[kProxRows - 1];
+    __syncthreads();
+    primal(p0, p1, row_r[wave][lane]);
+  }
+  const int c = lane - lo;
+#pragma unroll
+  for (int m = 0; m < kProxRows; ++m) {
+    const int row = wave * kProxRows + m - lo, gy = gy0 + m;
+    if (c < 0 || c >= s.tx || !in_x || row < 0 || row >= s.ty || gy >= g.n1) continue;
+    const long i = (long)gy * g.n0 + gx;
+    if (s.last) {
+      g.x[i] = x[m];
+    } else {
+      g.r[i] = r0[m];
+      g.r[N + i] = r1[m];
+      g.r[2 * N + i] = p0[m];
+      g.r[3 * N + i] = p1[m];
+    }
+  }
+}
+__global__ void __launch_bounds__(64 * kProxWaves) k_prox_steps(ProxImage g, ProxSteps s) {
+  prox_window(g, s, (int)blockIdx.x);
+}
+__global__ void __launch_bounds__(64 * kProxWaves) k_prox_steps_b(ProxBatch b, ProxSteps s) {
+  const int k = prox_image(b);
+  prox_window(ProxImage{b.g[k].n[0], b.g[k].n[1], b.z[k], b.lower[k], b.x[k], b.r[k], b.lam[k], b.step[k]}, s,
+              (int)blockIdx.x - b.begin[k]);
+}
+
 __global__ void k_proj(long n, const float* __restrict__ z, const float* __restrict__ lower, float* __restrict__ x) {
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) x[i] = fmaxf(z[i], lower ? lower[i] : 0.f);
@@ -406,6 +541,51 @@ int red_buffer(hipStream_t st, double** out) {
   return PAT_OK;
 }
 
+// Extrapolation factors of n_iter FGP iterations.
+std::vector<float> fgp_thetas(int n_iter) {
+  std::vector<float> th(n_iter);
+  double t = 1.0;
+  for (int k = 0; k < n_iter; ++k) {
+    const double tn = (1.0 + std::sqrt(1.0 + 4.0 * t * t)) / 2.0;
+    th[k] = (float)((t - 1.0) / tn);
+    t = tn;
+  }
+  return th;
+}
+
+// Iterations [k0, k0 + k) of n_iter in one launch, the last of them all the way to x.
+ProxSteps prox_steps(const std::vector<float>& th, int k0, int k) {
+  ProxSteps s{};
+  s.k = k;
+  s.first = k0 == 0;
+  s.last = k0 + k == (int)th.size();
+  s.tx = 64 - 2 * k - s.last;
+  s.ty = kProxH - 2 * k - s.last;
+  std::copy_n(th.begin() + k0, k, s.theta);
+  return s;
+}
+int prox_tiles(const Grid3& g, const ProxSteps& s) {
+  return ((g.n[0] + s.tx - 1) / s.tx) * ((g.n[1] + s.ty - 1) / s.ty);
+}
+bool disjoint(const float* a, const float* b, long n) { return !a || !b || a + n <= b || b + n <= a; }
+// Whether launches of several iterations can run the image: they read z and
+// lower around a point that another workgroup may already have written to x.
+bool prox_windows(const Grid3& g, int ndim, const float* z, const float* lower, const float* x) {
+  return ndim == 2 && disjoint(x, z, g.N) && disjoint(x, lower, g.N);
+}
+
+// [0, k0) and [k1, n_iter) run in one launch each, [k0, k1) two launches an
+// iteration: the workspace holds one copy of r and p_prev, which launches of
+// several iterations cannot update in place.  Up to 12 iterations one launch
+// is faster than two (14 iterations at 512^2: 31.9 us in one, 27.8 in two);
+// in halves a launch may take up to 16 (30 iterations: 67 us; 111 with at
+// most 12 and the rest two launches an iteration).
+constexpr int kProxOne = 12, kProxHalf = 16;
+void prox_split(int n_iter, int& k0, int& k1) {
+  k0 = n_iter <= kProxOne ? n_iter : std::min(kProxHalf, (n_iter + 1) / 2);
+  k1 = std::max(k0, n_iter - kProxHalf);
+}
+
 }  // namespace
 
 // ===================================================================== C entry points
@@ -441,13 +621,14 @@ extern "C" int pat_tv_prox_batched(int32_t count, int32_t ndim, const int32_t* n
       if (rc) return rc;
     }
   }
-  for (size_t k0 = 0; k0 < iter.size(); k0 += kProxBatch) {
+  const std::vector<float> th = fgp_thetas(n_iter);
+  for (size_t i0 = 0; i0 < iter.size(); i0 += kProxBatch) {
     ProxBatch b{};
-    b.count = (int)std::min<size_t>(kProxBatch, iter.size() - k0);
+    b.count = (int)std::min<size_t>(kProxBatch, iter.size() - i0);
     b.ndim = ndim;
-    b.begin[0] = 0;
+    bool windows = true;
     for (int j = 0; j < b.count; ++j) {
-      const int k = iter[k0 + j];
+      const int k = iter[i0 + j];
       make_grid(ndim, n + 3 * k, b.g[j]);
       b.z[j] = z[k];
       b.lower[j] = lower ? lower[k] : nullptr;
@@ -455,19 +636,31 @@ extern "C" int pat_tv_prox_batched(int32_t count, int32_t ndim, const int32_t* n
       b.r[j] = (float*)work[k];
       b.lam[j] = (float)lambda_eff[k];
       b.step[j] = (float)(1.0 / (4.0 * ndim * lambda_eff[k]));
-      b.begin[j + 1] = b.begin[j] + blocks_for(b.g[j].N);
+      windows = windows && prox_windows(b.g[j], ndim, b.z[j], b.lower[j], b.x[j]);
     }
-    const int nb = b.begin[b.count];
-    hipLaunchKernelGGL(k_prox_zero_b, dim3(nb), dim3(256), 0, st, b);
-    double t = 1.0;
-    for (int it = 0; it < n_iter; ++it) {
-      const double tn = (1.0 + std::sqrt(1.0 + 4.0 * t * t)) / 2.0;
-      const float theta = (float)((t - 1.0) / tn);
+    auto blocks = [&](auto&& of) {
+      b.begin[0] = 0;
+      for (int j = 0; j < b.count; ++j) b.begin[j + 1] = b.begin[j] + of(b.g[j]);
+      return b.begin[b.count];
+    };
+    auto steps = [&](int from, int k) {
+      const ProxSteps s = prox_steps(th, from, k);
+      const int nb = blocks([&](const Grid3& g) { return prox_tiles(g, s); });
+      hipLaunchKernelGGL(k_prox_steps_b, dim3(nb), dim3(64 * kProxWaves), 0, st, b, s);
+    };
+    int k0 = 0, k1 = n_iter;  // the iterations with launches of their own
+    if (windows) {
+      prox_split(n_iter, k0, k1);
+      if (k0 > 0) steps(0, k0);
+    }
+    const int nb = blocks([](const Grid3& g) { return blocks_for(g.N); });
+    if (k0 == 0) hipLaunchKernelGGL(k_prox_zero_b, dim3(nb), dim3(256), 0, st, b);
+    for (int it = k0; it < k1; ++it) {
       hipLaunchKernelGGL(k_prox_primal_b, dim3(nb), dim3(256), 0, st, b, 0);
-      hipLaunchKernelGGL(k_prox_dual_b, dim3(nb), dim3(256), 0, st, b, theta);
-      t = tn;
+      hipLaunchKernelGGL(k_prox_dual_b, dim3(nb), dim3(256), 0, st, b, th[it]);
     }
-    hipLaunchKernelGGL(k_prox_primal_b, dim3(nb), dim3(256), 0, st, b, 1);
+    if (k1 < n_iter) steps(k1, n_iter - k1);
+    else if (k0 < n_iter) hipLaunchKernelGGL(k_prox_primal_b, dim3(nb), dim3(256), 0, st, b, 1);
     if (hipGetLastError() != hipSuccess) return PAT_EHIP;
   }
   return PAT_OK;
@@ -487,18 +680,26 @@ int tv_prox_run(const Grid3& g, int ndim, const float* z, float* x, double lambd
   float* r = work;
   float* pprev = r + (long)ndim * g.N;
   float* xt = pprev + (long)ndim * g.N;
-  hipLaunchKernelGGL(k_zero, dim3(blocks_for(2L * ndim * g.N)), dim3(256), 0, st, 2L * ndim * g.N, r);
   const float lam = (float)lambda_eff;
   const float step = (float)(1.0 / (4.0 * ndim * lambda_eff));
-  double t = 1.0;
-  for (int k = 0; k < n_iter; ++k) {
-    const double tn = (1.0 + std::sqrt(1.0 + 4.0 * t * t)) / 2.0;
-    const float theta = (float)((t - 1.0) / tn);
-    hipLaunchKernelGGL(k_prox_primal, dim3(nb), dim3(256), 0, st, g, ndim, z, lower, r, lam, xt);
-    hipLaunchKernelGGL(k_prox_dual, dim3(nb), dim3(256), 0, st, g, ndim, xt, step, theta, r, pprev);
-    t = tn;
+  const std::vector<float> th = fgp_thetas(n_iter);
+  int k0 = 0, k1 = n_iter;  // the iterations with launches of their own
+  const ProxImage im{g.n[0], g.n[1], z, lower, x, r, lam, step};
+  auto steps = [&](int from, int k) {
+    const ProxSteps s = prox_steps(th, from, k);
+    hipLaunchKernelGGL(k_prox_steps, dim3(prox_tiles(g, s)), dim3(64 * kProxWaves), 0, st, im, s);
+  };
+  if (prox_windows(g, ndim, z, lower, x)) {
+    prox_split(n_iter, k0, k1);
+    if (k0 > 0) steps(0, k0);
   }
-  hipLaunchKernelGGL(k_prox_primal, dim3(nb), dim3(256), 0, st, g, ndim, z, lower, pprev, lam, x);
+  if (k0 == 0) hipLaunchKernelGGL(k_zero, dim3(blocks_for(2L * ndim * g.N)), dim3(256), 0, st, 2L * ndim * g.N, r);
+  for (int k = k0; k < k1; ++k) {
+    hipLaunchKernelGGL(k_prox_primal, dim3(nb), dim3(256), 0, st, g, ndim, z, lower, r, lam, xt);
+    hipLaunchKernelGGL(k_prox_dual, dim3(nb), dim3(256), 0, st, g, ndim, xt, step, th[k], r, pprev);
+  }
+  if (k1 < n_iter) steps(k1, n_iter - k1);
+  else if (k0 < n_iter) hipLaunchKernelGGL(k_prox_primal, dim3(nb), dim3(256), 0, st, g, ndim, z, lower, pprev, lam, x);
   return hipGetLastError() == hipSuccess ? PAT_OK : PAT_EHIP;
 }
 
