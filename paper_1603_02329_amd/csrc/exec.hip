@@ -411,17 +411,23 @@ bool resident(const pat_plan* p) { return solve_shape(p->desc.ndim, p->hp.n[0], 
 // one to 64 instances of 64^2 to 512^2).  A resident step takes
 // 14 us + 0.28 us per 1000 points on its die, the dies working side by side
 // and each holding 32 / members domains; over every die 30 us + 0.037 us per
-// 1000 points, one instance at a time.  A step of the batched launches takes
-// 42 us + 0.02 us per 1000 points of all its instances.
+// 1000 points, one instance at a time.  The instances over every die and
+// those on one run side by side too, at 0.4 of the shorter part's time:
+// 512^2 (600 steps) with 256^2 (300) 25.1 ms, 23.8 ms and 8.7 ms alone.  A
+// step of the batched launches takes 42 us + 0.02 us per 1000 points of all
+// its instances, 54 us when they have several shapes (512^2 with 256^2 60 us,
+// 4 of 128^2 with 4 of 256^2 65 us).
 bool resident_pays(pat_plan* const* plans, int nb) {
   double die[kSolveXcds] = {}, whole = 0, longest = 0, work = 0, steps_max = 1;
   std::vector<double> cost;  // time on a die, by the share of it that the instance holds
+  bool one_shape = true;
   if (nb > kSolveQueue) return false;
   for (int i = 0; i < nb; ++i) {
     const pat_plan* p = plans[i];
     if (!resident(p)) return false;
     const int nx = p->hp.n[0], ny = p->hp.n[1];
     const double steps = std::max(0, p->desc.nt - 1), kpts = 1e-3 * (double)p->npoints;
+    one_shape = one_shape && nx == plans[0]->hp.n[0] && ny == plans[0]->hp.n[1];
     steps_max = std::max(steps_max, steps);
     work += steps * kpts;
     if (solve_whole(nx, ny)) {
@@ -434,8 +440,9 @@ bool resident_pays(pat_plan* const* plans, int nb) {
   }
   std::sort(cost.rbegin(), cost.rend());
   for (double c : cost) *std::min_element(die, die + kSolveXcds) += c;
-  const double t_res = whole + std::max(longest, *std::max_element(die, die + kSolveXcds));
-  return t_res < steps_max * 42.0 + 0.02 * work;
+  const double dies = std::max(longest, *std::max_element(die, die + kSolveXcds));
+  const double t_res = std::max(whole, dies) + 0.4 * std::min(whole, dies);
+  return t_res < steps_max * (one_shape ? 42.0 : 54.0) + 0.02 * work;
 }
 
 SolveArgs solve_args(void* ctl, int domains) {

@@ -66,11 +66,17 @@ def test_resident_segments_bitwise():
         assert torch.equal(d, ref), n
 
 
-def test_resident_batch_bitwise():
-    """Several shapes and physics, more instances of one shape than dies."""
-    specs = [dict(n=(64, 64), nt=9 + k, ns=5, pml=4, lossy=True) for k in range(11)]
-    specs += [dict(n=(64, 128), nt=14, ns=40, pml=4, lossy=False), dict(n=(32, 64), nt=1, ns=3, pml=4, lossy=True),
-              dict(n=(32, 32), nt=20, ns=3, pml=4, lossy=True)]
+@pytest.mark.parametrize("which", ["dies", "all dies and one"])
+def test_resident_batch_bitwise(which):
+    """Several shapes and physics, more instances of one shape than dies; a
+    grid over every die beside grids on one."""
+    if which == "dies":
+        specs = [dict(n=(64, 64), nt=9 + k, ns=5, pml=4, lossy=True) for k in range(11)]
+        specs += [dict(n=(64, 128), nt=14, ns=40, pml=4, lossy=False), dict(n=(32, 64), nt=1, ns=3, pml=4, lossy=True),
+                  dict(n=(32, 32), nt=20, ns=3, pml=4, lossy=True)]
+    else:
+        specs = [dict(n=(512, 512), nt=21, ns=30, pml=8, lossy=True), dict(n=(256, 256), nt=11, ns=30, pml=8, lossy=True),
+                 dict(n=(128, 32), nt=40, ns=30, pml=8, lossy=False)]
     cases = [_case(100 + k, **s) for k, s in enumerate(specs)]
     plans, p0, h = zip(*cases)
     b = pat.Batch(plans)
