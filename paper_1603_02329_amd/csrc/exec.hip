@@ -409,8 +409,8 @@ bool resident(const pat_plan* p) { return solve_shape(p->desc.ndim, p->hp.n[0], 
 // Whether a batch runs as resident solves: when their estimated time is below
 // that of the batched launches (microseconds, forward, lossy; measured from
 // one to 64 instances of 64^2 to 512^2).  A resident step takes
-// 14 us + 0.28 us per 1000 points on its die, the dies working side by side
-// and each holding 32 / members domains; over every die 30 us + 0.037 us per
+// 13 us + 0.21 us per 1000 points on its die, the dies working side by side
+// and each holding 32 / members domains; over every die 24 us + 0.05 us per
 // 1000 points, one instance at a time.  The instances over every die and
 // those on one run side by side too, at 0.4 of the shorter part's time:
 // 512^2 (600 steps) with 256^2 (300) 25.1 ms, 23.8 ms and 8.7 ms alone.  A
@@ -431,9 +431,9 @@ bool resident_pays(pat_plan* const* plans, int nb) {
     steps_max = std::max(steps_max, steps);
     work += steps * kpts;
     if (solve_whole(nx, ny)) {
-      whole += steps * (30.0 + 0.037 * kpts);
+      whole += steps * (24.0 + 0.05 * kpts);
     } else {
-      const double t = steps * (14.0 + 0.28 * kpts);
+      const double t = steps * (13.0 + 0.21 * kpts);
       longest = std::max(longest, t);
       cost.push_back(t * solve_members(nx, ny) / kSolveCus);
     }

@@ -18,19 +18,26 @@
 // the two outputs of the transposed density update) on different wavefronts,
 // so that no wavefront runs more than two transforms between two barriers,
 // and as few wavefronts per compute unit as there are compute units for.
-// What bounds it is the chain of one wavefront: load latency, some 4 cycles
-// per instruction, four exchanges per transform and the barrier.
+// What bounds it is the chain of one wavefront: some 4 cycles per
+// instruction, four exchanges per transform, and the barrier (stores complete
+// after 0.27 us, a load from the L2 takes 0.09 us).  So what does not change
+// through the time loop is not formed in it (the columns' multipliers stay in
+// registers), and the loads of a pass's own rows stand between the two halves
+// of the barrier.
 //
-// Per step of the time loop, launches and resident (us): lossless forward
-// 64^2 22.5 and 10.7; lossy forward 64^2 32.9 and 15.3, 128^2 36.7 and 20.8,
-// 256 x 64 40.6 and 21.2, 256^2 43.9 and 28.9, 512^2 53.7 and 39.8; the
-// adjoint within 5% of the forward.
+// Per step of the time loop, launches, resident, and resident with these two
+// (us): lossless forward 64^2 22.5, 10.7, 9.5; lossy forward 64^2 32.9, 15.3,
+// 12.9, 128^2 36.7, 20.8, 17.7-19.4 (by die), 256 x 64 40.6, 20.0, 17.3, 256^2
+// 43.9, 28.9, 26.3, 512^2 53.7, 39.8, 35.4; the adjoint within 5% of the
+// forward.
 //
 // Membership is dynamic, so that a domain never waits for a workgroup that
 // is not running: a domain's roll is closed when it is complete or after a
 // short time, and a workgroup that comes later leaves at once.  Every
 // member is then resident until the queue is empty.  Every wait is bounded.
 #pragma once
+
+#include <type_traits>
 
 #include "passes_col.h"
 #include "passes_row.h"
@@ -339,45 +346,45 @@ struct Domain {
     return (int32_t)(PAT_AGENT_LD(w) - epoch) >= 0;
   }
 
-  // All members' stores of the pass are complete and their next loads come
-  // after.  False once any wait of this block has run out.
-  __device__ __forceinline__ bool barrier() {
+  // The barrier between two passes, in two halves: arrive() once this block's
+  // stores of the pass are issued, wait() before its first load of what other
+  // members stored.  Loads of the block's own rows go between the two.
+  __device__ __forceinline__ void arrive() {
     ++epoch;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
+    if (n > 1 && threadIdx.x < 64) {
+      const int lane = (int)threadIdx.x;
+      if (!WHOLE || xr != 0) {
+        if (lane == 0) PAT_AGENT_ST(&flag[xr], epoch);
+      } else {
+        // the first member of a die waits for its others
+        for (int k = 1; k < nx; k += 64) poll(&flag[k + lane < nx ? k + lane : k]);
+        if (lane == 0) PAT_AGENT_ST(&d->lead[x * kSolveLine], epoch);
+      }
+    }
+  }
+  __device__ __forceinline__ void wait() {
     if (n > 1) {
       if (threadIdx.x < 64) {
         const int lane = (int)threadIdx.x;
-        int spin = 0;
-        if (!WHOLE || xr != 0) {
-          if (lane == 0) PAT_AGENT_ST(&flag[xr], epoch);
-        }
-        if (!WHOLE) {
-          const uint32_t* w = &flag[lane < nx ? lane : xr];
-          while (!__all(reached(w, epoch)) && ++spin < kSolveSpin) {
-          }
-        } else if (xr == 0) {
-          // the first member of a die waits for its others
-          for (int k = 1; k < nx; k += 64) {
-            const uint32_t* w = &flag[k + lane < nx ? k + lane : k];
-            while (!__all(reached(w, epoch)) && ++spin < kSolveSpin) {
-            }
-          }
-        }
-        if (WHOLE) {
-          if (xr == 0 && lane == 0) PAT_AGENT_ST(&d->lead[x], epoch);
-          const uint32_t* w = &d->lead[(dies >> (lane & 7)) & 1 ? (lane & 7) : x];
-          while (!__all(reached(w, epoch)) && ++spin < kSolveSpin) {
-          }
-        }
-        if (spin >= kSolveSpin && lane == 0) sh->fail = 1;
+        if (!WHOLE) poll(&flag[lane < nx ? lane : xr]);
+        else poll(&d->lead[((dies >> (lane & 7)) & 1 ? (lane & 7) : x) * kSolveLine]);
       }
       __syncthreads();
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    return n == 1 || __builtin_amdgcn_readfirstlane(sh->fail) == 0;
   }
+  // until every lane's word has reached this barrier; marks the block when that never happens
+  __device__ __forceinline__ void poll(const uint32_t* w) {
+    int spin = 0;
+    while (!__all(reached(w, epoch)) && ++spin < kSolveSpin) {
+    }
+    if (spin >= kSolveSpin && (threadIdx.x & 63) == 0) sh->fail = 1;
+  }
+  // whether a wait of this block has run out
+  __device__ __forceinline__ bool failed() const { return n > 1 && __builtin_amdgcn_readfirstlane(sh->fail) != 0; }
 };
 
 // Joins a domain of this block's die (WHOLE: the one domain); false for a
@@ -553,7 +560,7 @@ __device__ __forceinline__ void solve_r2c_products(const float2 (&a)[G::ER], con
 // Arithmetic as the row pass of the same kind (passes_row.h).
 template <int NX, int NY, int K>
 __device__ __forceinline__ void solve_row_part(const DevPlan& P, int unit, int j, int it, int wave,
-                                               SolveLds<NX, NY>& sh) {
+                                               Domain<solve_whole(NX, NY)>& dm, bool first_unit, SolveLds<NX, NY>& sh) {
   using G = SolveGeo<NX, NY>;
   constexpr int E = G::ER, T = G::TR, M = G::M, RL = G::RL;
   const int lane = opaque((int)(threadIdx.x & 63));
@@ -567,7 +574,9 @@ __device__ __forceinline__ void solve_row_part(const DevPlan& P, int unit, int j
   float2* mine = sh.px + wave * 64 * E;
   const float2* other = sh.px + (wave ^ (G::NW / 2)) * 64 * E;
   const auto& tws = sh.row_tw;
+  // the spectrum of the pass before: after every load of this member's own
   auto lds = [&](const float2* a, float2(&v)[E]) {
+    if (first_unit) dm.wait();
 #pragma unroll
     for (int m = 0; m < E; ++m) v[m] = gld_agent(a, base + T * m);
   };
@@ -628,11 +637,11 @@ __device__ __forceinline__ void solve_row_part(const DevPlan& P, int unit, int j
   if constexpr (K == R_FWD_1 || K == R_ADJ_1) {
     const bool first = (it == 0), last = (K == R_ADJ_1) && (it == P.nt - 2);
     float2 d[E], b[E], u[E], qs[E];
-    lds(P.S[1 + j], d);
     ldf(P.B[j], b);
     if (first) zero(u);
     else ldf(P.u[j], u);
     pml(P.Qsg, qs);
+    lds(P.S[1 + j], d);
     solve_c2r<G, NX>(d, L, t, h, tws);
 #pragma unroll
     for (int m = 0; m < E; ++m) {
@@ -647,12 +656,12 @@ __device__ __forceinline__ void solve_row_part(const DevPlan& P, int unit, int j
     out(d, P.S[1 + j]);
   } else if constexpr (K == R_FWD_2 || K == R_FWD_2LL) {
     float2 g[E], r[E], dr[E], q[E], v[E];
-    lds(P.S[1 + j], g);
     ldf(P.r[j], r);
     ldf(P.dtr0, dr);
     pml(P.Q, q);
     float2 c2[E];
     if constexpr (K == R_FWD_2LL) ldf(P.c2, c2);
+    lds(P.S[1 + j], g);
     solve_c2r<G, NX>(g, L, t, h, tws);
     // rho_j <- Q (Q rho_j - t_j), t_j = dt rho0 g_j
 #pragma unroll
@@ -684,7 +693,6 @@ __device__ __forceinline__ void solve_row_part(const DevPlan& P, int unit, int j
   } else if constexpr (K == R_FWD_3) {
     // part 0 transforms A1, part 1 A2 for part 0's equation of state
     float2 a[E], c2[E], r0[E], r1[E], ct[E], ce[E];
-    lds(P.S[1 + j], a);
     if (j == 0) {
       ldf(P.c2, c2);
       ldf(P.r[0], r0);
@@ -696,6 +704,7 @@ __device__ __forceinline__ void solve_row_part(const DevPlan& P, int unit, int j
         absorption_coefs<E>(P, c2, ct, ce);
       }
     }
+    lds(P.S[1 + j], a);
     solve_c2r<G, NX>(a, L, t, h, tws);
     if (j == 1) send(a);
     __syncthreads();
@@ -712,8 +721,6 @@ __device__ __forceinline__ void solve_row_part(const DevPlan& P, int unit, int j
     const bool first = (it == 0);
     const int nsamp = P.nt - 1 - it;
     float2 v[E], c2[E], cf[E], q[E], r[E];
-    if (first) zero(v);
-    else lds(P.S[0], v);
     ldf(P.c2, c2);
     if constexpr (K == R_ADJ_3) {
       if (!P.alpha_uniform) ldf(j == 0 ? P.c2eta : P.c2tau, cf);
@@ -739,6 +746,8 @@ __device__ __forceinline__ void solve_row_part(const DevPlan& P, int unit, int j
         for (int m = 0; m < E; ++m) cf[m] = j == 0 ? ce[m] : ct[m];
       }
     }
+    if (first) zero(v);
+    else lds(P.S[0], v);
     if (!first) solve_c2r<G, NX>(v, L, t, h, tws);
 #pragma unroll
     for (int m = 0; m < E; ++m) L[e0 + T * m] = v[m];
@@ -780,12 +789,12 @@ __device__ __forceinline__ void solve_row_part(const DevPlan& P, int unit, int j
     // part 0 transforms A2, part 1 A1; both then update their component
     const bool first = (it == 0);
     float2 a[E], v[E], q[E], dr[E], qq[E], r[E];
-    lds(P.S[1 + j], a);
     ldf(P.q, q);
     ldf(P.dtr0, dr);
     pml(P.Q, qq);
     if (first) zero(r);
     else ldf(P.r[j], r);
+    lds(P.S[1 + j], a);
     solve_c2r<G, NX>(a, L, t, h, tws);
     send(a);
     __syncthreads();
@@ -803,16 +812,41 @@ __device__ __forceinline__ void solve_row_part(const DevPlan& P, int unit, int j
 // Row pass of every unit of this member: wavefronts 0 .. NW/2 - 1 run part 0,
 // the others part 1 of the same rows.
 template <int NX, int NY, int K>
-__device__ __forceinline__ void solve_row(const DevPlan& P, int it, const Domain<solve_whole(NX, NY)>& dm,
+__device__ __forceinline__ void solve_row(const DevPlan& P, int it, Domain<solve_whole(NX, NY)>& dm,
                                           SolveLds<NX, NY>& sh) {
   using G = SolveGeo<NX, NY>;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int j = wave / (G::NW / 2);
   for (int g = dm.rank; g < G::groups; g += dm.n) {
     if (g != dm.rank) __syncthreads();  // what the parts handed each other has been read
-    solve_row_part<NX, NY, K>(P, g * (G::NW / 2) + wave % (G::NW / 2), j, it, wave, sh);
+    solve_row_part<NX, NY, K>(P, g * (G::NW / 2) + wave % (G::NW / 2), j, it, wave, dm, g == dm.rank, sh);
   }
 }
+
+// The multipliers of one column pass at this lane's elements: at its x-bin
+// and, for the packed column 0, the second factor of its mirror bins.  A
+// member keeps the tiles it has through the time loop, and their multipliers
+// stay in registers (unit: whose they are).
+template <int E>
+struct ColMult {
+  float2 mv[E], mN[E];
+  int unit;
+  __device__ __forceinline__ float2 at(int m) const { return mv[m]; }
+  __device__ __forceinline__ float2 mirror(int m) const { return mN[m]; }
+  __device__ __forceinline__ void set(int m, float2 v) { mv[m] = v; }
+  __device__ __forceinline__ void set_mirror(int m, float2 v) { mN[m] = v; }
+};
+template <int E>
+struct RealMult {  // Laplacians: real
+  float mv[E], mN[E];
+  int unit;
+  __device__ __forceinline__ float2 at(int m) const { return f2(mv[m], 0.f); }
+  __device__ __forceinline__ float2 mirror(int m) const { return f2(mN[m], 0.f); }
+  __device__ __forceinline__ void set(int m, float2 v) { mv[m] = v.x; }
+  __device__ __forceinline__ void set_mirror(int m, float2 v) { mN[m] = v.x; }
+};
+template <int E, int FAM>
+using MultOf = typename std::conditional<FAM == F_ABS, RealMult<E>, ColMult<E>>::type;
 
 // One column pass over tile `tile` of NTHT threads (mapping and transforms as
 // colm_pass): part j's input, multiplier and output.
@@ -820,7 +854,9 @@ __device__ __forceinline__ void solve_row(const DevPlan& P, int it, const Domain
 //   MODE 2  S[0] <- m_0 S[1] + m_1 S[2], the parts in the two halves of the block
 // SWAP (Laplacians): part 0 applies |k|^(y-1), part 1 |k|^(y-2)/dt.
 template <int NX, int NY, int MODE, int FAM, int SWAP>
-__device__ __forceinline__ void solve_col_part(const DevPlan& P, int tile, int j, SolveLds<NX, NY>& sh) {
+__device__ __forceinline__ void solve_col_part(const DevPlan& P, int tile, int j, int unit,
+                                               Domain<solve_whole(NX, NY)>& dm, bool first_unit, SolveLds<NX, NY>& sh,
+                                               MultOf<SolveGeo<NX, NY>::EC, FAM>& cm) {
   using G = SolveGeo<NX, NY>;
   constexpr int NTHT = MODE == 2 ? G::NTH / 2 : G::NTH;
   constexpr int E = G::EC, TC = G::TC, LDT = G::LDT, TILE = NTHT / G::CL, M = G::M;
@@ -842,22 +878,18 @@ __device__ __forceinline__ void solve_col_part(const DevPlan& P, int tile, int j
   const int ka = c0 + (valid ? ca : 0), kb = c0 + ((M >= TILE || cb < M) ? cb : 0);
   const bool special = tile == 0, fix = special && cb == 0;  // packed column 0
 
-  const float2* src = MODE == 0 ? P.S[0] : P.S[1 + j];
-  float2 v[E], s[E];
-#pragma unroll
-  for (int m = 0; m < E; ++m) v[m] = gld_agent(src, (long)(ea + TC * m) * M + ka);
   // multipliers of this lane's elements (mapping B), at x-bin kb and, for the
   // packed column 0, at x-bin NX / 2
   constexpr bool DERIV = FAM != F_ABS;
-  float2 mv[E], mN[E];
   // packed column 0 holds C = A + iB: 1/2 (m0 + mN) C + 1/2 (m0 - mN) conj(C(-k)),
   // mN = g sh; mN[] takes the second factor there
   auto packed = [&](int m, float g, float2 sh) {
-    const float2 gg = f2(g, g), p = 0.5f * fma2(gg, sh, mv[m]), q = 0.5f * fma2(neg2(gg), sh, mv[m]);
-    mN[m] = q;
-    mv[m] = sel2(fix, p, mv[m]);
+    const float2 gg = f2(g, g), p = 0.5f * fma2(gg, sh, cm.at(m)), q = 0.5f * fma2(neg2(gg), sh, cm.at(m));
+    cm.set_mirror(m, q);
+    cm.set(m, sel2(fix, p, cm.at(m)));
   };
-  {
+  if (cm.unit != unit) {
+    cm.unit = unit;
     const float k2x = gld(P.ksq[0], kb), k2N = gld(P.ksq[0], M);
     float k2[E];
 #pragma unroll
@@ -876,7 +908,7 @@ __device__ __forceinline__ void solve_col_part(const DevPlan& P, int tile, int j
       }
 #pragma unroll
       for (int m = 0; m < E; ++m) {
-        mv[m] = scl2(sinc_sqrt(P.kap2 * (k2x + k2[m])) * P.scale, sx[m]);
+        cm.set(m, scl2(sinc_sqrt(P.kap2 * (k2x + k2[m])) * P.scale, sx[m]));
         if (special) packed(m, sinc_sqrt(P.kap2 * (k2N + k2[m])) * P.scale, j == 0 ? sN : sx[m]);
       }
     } else {
@@ -889,11 +921,16 @@ __device__ __forceinline__ void solve_col_part(const DevPlan& P, int tile, int j
       };
 #pragma unroll
       for (int m = 0; m < E; ++m) {
-        mv[m] = f2(lapl(k2x + k2[m]) * P.scale, 0.f);
+        cm.set(m, f2(lapl(k2x + k2[m]) * P.scale, 0.f));
         if (special) packed(m, lapl(k2N + k2[m]), f2(P.scale, 0.f));
       }
     }
   }
+  if (first_unit) dm.wait();
+  const float2* src = MODE == 0 ? P.S[0] : P.S[1 + j];
+  float2 v[E], s[E];
+#pragma unroll
+  for (int m = 0; m < E; ++m) v[m] = gld_agent(src, (long)(ea + TC * m) * M + ka);
   SolveStage<PC, NY, -1, 1, 8>::run(v, La, ta, h, nullptr);
   sync();
 #pragma unroll
@@ -908,11 +945,11 @@ __device__ __forceinline__ void solve_col_part(const DevPlan& P, int tile, int j
     }
     WaveSync::sync();
 #pragma unroll
-    for (int m = 0; m < E; ++m) w[m] = cmul(mN[m], conjf2(Lb[(NY - (eb + TC * m)) & (NY - 1)]));
+    for (int m = 0; m < E; ++m) w[m] = cmul(cm.mirror(m), conjf2(Lb[(NY - (eb + TC * m)) & (NY - 1)]));
     WaveSync::sync();
   }
 #pragma unroll
-  for (int m = 0; m < E; ++m) v[m] = cmul(mv[m], s[m]);
+  for (int m = 0; m < E; ++m) v[m] = cmul(cm.at(m), s[m]);
   if (fix && (MODE != 2 || j == 0)) {
 #pragma unroll
     for (int m = 0; m < E; ++m) v[m] = v[m] + w[m];
@@ -951,7 +988,8 @@ __device__ __forceinline__ void solve_col_part(const DevPlan& P, int tile, int j
 }
 
 template <int NX, int NY, int MODE, int FAM, int SWAP = 0>
-__device__ __forceinline__ void solve_col(const DevPlan& P, const Domain<solve_whole(NX, NY)>& dm, SolveLds<NX, NY>& sh) {
+__device__ __forceinline__ void solve_col(const DevPlan& P, Domain<solve_whole(NX, NY)>& dm, SolveLds<NX, NY>& sh,
+                                          MultOf<SolveGeo<NX, NY>::EC, FAM>& cm) {
   using G = SolveGeo<NX, NY>;
   constexpr int NTHT = MODE == 2 ? G::NTH / 2 : G::NTH;
   constexpr int TILE = NTHT / G::CL, tiles = (G::M + TILE - 1) / TILE;
@@ -960,7 +998,7 @@ __device__ __forceinline__ void solve_col(const DevPlan& P, const Domain<solve_w
   for (int u = dm.rank; u < units; u += dm.n) {
     if (u != dm.rank) __syncthreads();  // the previous tile's last reads of the regions
     const int j = MODE == 2 ? wave / (G::NW / 2) : (u >= tiles ? 1 : 0);
-    solve_col_part<NX, NY, MODE, FAM, SWAP>(P, MODE == 2 ? u : u - j * tiles, j, sh);
+    solve_col_part<NX, NY, MODE, FAM, SWAP>(P, MODE == 2 ? u : u - j * tiles, j, u, dm, u == dm.rank, sh, cm);
   }
 }
 
@@ -971,9 +1009,13 @@ __device__ __forceinline__ void give_up(const DevPlan& P) {
 
 // ---------------------------------------------------------------- the kernel
 // Steps [s0, s1) (s1 < 0: to the last) of direction DIR of every queued
-// instance, between the launches of the initial and the final pass.
+// instance, between the launches of the initial and the final pass.  At most
+// 168 registers, three wavefronts per SIMD: with 188 only two domains over
+// every die fit side by side, and the members that a third one missed cost it
+// its speed (three 512^2 adjoints and three 64^2 forwards on streams of their
+// own, 200 steps: 43 ms, 14 ms with 168; launches 21 ms).
 template <int NX, int NY, int DIR, int LOSSY>
-__global__ void __launch_bounds__((SolveGeo<NX, NY>::NTH)) k_solve(SolveArgs a) {
+__global__ void __launch_bounds__((SolveGeo<NX, NY>::NTH), 3) k_solve(SolveArgs a) {
   using G = SolveGeo<NX, NY>;
   constexpr int WHOLE = G::WHOLE;
   __shared__ SolveLds<NX, NY> sh;
@@ -987,42 +1029,46 @@ __global__ void __launch_bounds__((SolveGeo<NX, NY>::NTH)) k_solve(SolveArgs a) 
     if (inst < 0) return;
     const DevPlan& P = *constant(a.list ? a.list[inst] : a.one);
     const int s1 = a.s1 < 0 ? P.nt - 1 : a.s1;
+    ColMult<G::EC> ma, mb;
+    RealMult<G::EC> ml;
+    ma.unit = mb.unit = ml.unit = -1;
     for (int it = a.s0; it < s1; ++it) {
       if constexpr (DIR == 0) {
-        solve_col<NX, NY, 0, F_A>(P, dm, sh);
-        if (!dm.barrier()) return give_up(P);
+        solve_col<NX, NY, 0, F_A>(P, dm, sh, ma);
+        dm.arrive();
         solve_row<NX, NY, R_FWD_1>(P, it, dm, sh);
-        if (!dm.barrier()) return give_up(P);
-        solve_col<NX, NY, 1, F_B>(P, dm, sh);
-        if (!dm.barrier()) return give_up(P);
+        dm.arrive();
+        solve_col<NX, NY, 1, F_B>(P, dm, sh, mb);
+        dm.arrive();
         if constexpr (LOSSY) {
           solve_row<NX, NY, R_FWD_2>(P, it, dm, sh);
-          if (!dm.barrier()) return give_up(P);
-          solve_col<NX, NY, 1, F_ABS, 0>(P, dm, sh);
-          if (!dm.barrier()) return give_up(P);
+          dm.arrive();
+          solve_col<NX, NY, 1, F_ABS, 0>(P, dm, sh, ml);
+          dm.arrive();
           solve_row<NX, NY, R_FWD_3>(P, it, dm, sh);
         } else {
           solve_row<NX, NY, R_FWD_2LL>(P, it, dm, sh);
         }
-        if (!dm.barrier()) return give_up(P);
+        dm.arrive();
       } else {
         if constexpr (LOSSY) {
           solve_row<NX, NY, R_ADJ_3>(P, it, dm, sh);
-          if (!dm.barrier()) return give_up(P);
-          solve_col<NX, NY, 1, F_ABS, 1>(P, dm, sh);
-          if (!dm.barrier()) return give_up(P);
+          dm.arrive();
+          solve_col<NX, NY, 1, F_ABS, 1>(P, dm, sh, ml);
+          dm.arrive();
           solve_row<NX, NY, R_ADJ_2>(P, it, dm, sh);
         } else {
           solve_row<NX, NY, R_ADJ_32LL>(P, it, dm, sh);
         }
-        if (!dm.barrier()) return give_up(P);
-        solve_col<NX, NY, 1, F_A>(P, dm, sh);
-        if (!dm.barrier()) return give_up(P);
+        dm.arrive();
+        solve_col<NX, NY, 1, F_A>(P, dm, sh, ma);
+        dm.arrive();
         solve_row<NX, NY, R_ADJ_1>(P, it, dm, sh);
-        if (!dm.barrier()) return give_up(P);
-        solve_col<NX, NY, 2, F_B>(P, dm, sh);
-        if (!dm.barrier()) return give_up(P);
+        dm.arrive();
+        solve_col<NX, NY, 2, F_B>(P, dm, sh, mb);
+        dm.arrive();
       }
+      if (dm.failed()) return give_up(P);
     }
   }
 }

@@ -14,8 +14,9 @@ constexpr uint32_t kSolveClosed = 0x80000000u;
 constexpr uint64_t kSolveRollTicks = 10000;  // of the 100 MHz clock
 
 // Grids above this run on one domain over every die, the others on one die.
-// Per step (forward, lossy), on one die and over all: 256^2 27.8 and 30.6 us;
-// 512 x 128 27.0 and 29.5; 512 x 256 50.2 and 31.5; 512^2 87.6 and 39.5.
+// Per step (forward, lossy, before the multipliers stayed in registers), on
+// one die and over all: 256^2 27.8 and 30.6 us; 512 x 128 27.0 and 29.5;
+// 512 x 256 50.2 and 31.5; 512^2 87.6 and 39.5.
 constexpr int kSolveDiePoints = 65536;
 constexpr bool solve_whole(int nx, int ny) { return nx * ny > kSolveDiePoints; }
 // Rows and columns are carried by two lanes where the per-launch passes have
@@ -42,11 +43,14 @@ constexpr int solve_members(int nx, int ny) {
 }
 
 // One domain: its roll, the instance its first member claimed, and the
-// barrier words: a flag per member, die by die, and one word per die.
+// barrier words: a flag per member, die by die, and one word per die, each on
+// a line of its own (on one line, every die's store takes it from all others:
+// 512^2 38.3 us per step, 36.0 apart).
+constexpr int kSolveLine = 32;  // words
 struct alignas(128) SolveDom {
   uint32_t roll, n, claim, ready;
   uint32_t count[kSolveXcds];  // members per die (domains over every die)
-  alignas(128) uint32_t lead[kSolveXcds];
+  alignas(128) uint32_t lead[kSolveXcds * kSolveLine];
   alignas(128) uint32_t flag[kSolveXcds * kSolveCus];
 };
 struct alignas(128) SolveCtl {
