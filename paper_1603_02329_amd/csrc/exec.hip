@@ -464,6 +464,7 @@ int solve_one(const pat_plan* p, int dir, int s0, int s1, hipStream_t st) {
   a.members = solve_members(p->hp.n[0], p->hp.n[1]);
   a.s0 = s0;
   a.s1 = s1;
+  a.solve_ticks = solve_ticks(s1 - s0);
   return launch_solve(p->hp.n[0], p->hp.n[1], dir, p->lossy, a, st) == hipSuccess ? PAT_OK : PAT_EHIP;
 }
 
@@ -683,6 +684,7 @@ struct pat_batch {
     void* ctl = nullptr;
     int first[kSolveXcds + 1] = {};
     int members = 0, domains = 0;
+    long steps = 0;  // of its longest instance
   };
   bool resident = false;
   std::vector<Queue> queue;
@@ -835,6 +837,7 @@ int batch_run_resident(pat_batch* b, int dir, const float* const* in, float* con
     SolveArgs a = solve_args(q.ctl, q.domains);
     a.list = q.list;
     a.members = q.members;
+    a.solve_ticks = solve_ticks(q.steps);
     for (int x = 0; x <= kSolveXcds; ++x) a.first[x] = q.first[x];
     hipStream_t s = k == 0 ? st : b->lanes[(k - 1) % b->lanes.size()];
     if (k > 0 && hipStreamWaitEvent(s, b->fork, 0) != hipSuccess) return PAT_EHIP;
@@ -1152,6 +1155,7 @@ extern "C" int pat_batch_create_ex(pat_batch** out, pat_plan* const* plans, int3
       auto& q = b->queue.back();
       std::tie(q.nx, q.ny, q.lossy) = sh.first;
       for (const auto& w : work) {
+        q.steps = std::max(q.steps, (long)b->cls[w.k].plans[w.i]->desc.nt - 1);
         const int x = (int)(std::min_element(load, load + kSolveXcds) - load);
         q.order[x].emplace_back(w.k, w.i);
         load[x] += w.w;

@@ -33,7 +33,7 @@
 //
 // Membership is dynamic, so that a domain never waits for a workgroup that
 // is not running: a domain's roll is closed when it is complete or after a
-// short time, and a workgroup that comes later leaves at once.  Every
+// bounded time, and a workgroup that comes later leaves at once.  Every
 // member is then resident until the queue is empty.  Every wait is bounded.
 #pragma once
 
@@ -357,11 +357,12 @@ struct Domain {
     if (n > 1 && threadIdx.x < 64) {
       const int lane = (int)threadIdx.x;
       if (!WHOLE || xr != 0) {
-        if (lane == 0) PAT_AGENT_ST(&flag[xr], epoch);
+        if (lane == 0) PAT_AGENT_ST(&flag[solve_flag(xr)], epoch);
       } else {
         // the first member of a die waits for its others
-        for (int k = 1; k < nx; k += 64) poll(&flag[k + lane < nx ? k + lane : k]);
-        if (lane == 0) PAT_AGENT_ST(&d->lead[x * kSolveLine], epoch);
+        for (int k = 1; k < nx; k += 64) poll(&flag[solve_flag(k + lane < nx ? k + lane : k)]);
+        // (a copy per die: its members poll lines that no other die's poll)
+        if (lane < kSolveXcds) PAT_AGENT_ST(&d[lane].lead[x * kSolveLine], epoch);
       }
     }
   }
@@ -369,8 +370,8 @@ struct Domain {
     if (n > 1) {
       if (threadIdx.x < 64) {
         const int lane = (int)threadIdx.x;
-        if (!WHOLE) poll(&flag[lane < nx ? lane : xr]);
-        else poll(&d->lead[((dies >> (lane & 7)) & 1 ? (lane & 7) : x) * kSolveLine]);
+        if (!WHOLE) poll(&flag[solve_flag(lane < nx ? lane : xr)]);
+        else poll(&d[x].lead[((dies >> (lane & 7)) & 1 ? (lane & 7) : x) * kSolveLine]);
       }
       __syncthreads();
     }
@@ -407,9 +408,17 @@ __device__ __forceinline__ bool join_domain(const SolveArgs& a, SolveShared& sh,
         int spin = 0;
         uint32_t v = 1;
         if (old == 0) {
-          // the first member closes the roll: complete, or after 100 us
+          // The first member closes the roll: complete, or once it has waited
+          // as long as the solve would take longer with the members there
+          // (n of m take ceil(m / n) times the time), or when no instance is left.
           const uint64_t t0 = wall_clock64();
-          while (v < (uint32_t)a.members && wall_clock64() - t0 < kSolveRollTicks) v = PAT_AGENT_LD(&d->roll);
+          for (;;) {
+            v = PAT_AGENT_LD(&d->roll);
+            const uint64_t more = ((uint32_t)a.members + v - 1) / v - 1, waited = wall_clock64() - t0;
+            if (more == 0 || waited >= more * a.solve_ticks || waited >= kSolveRollTicks ||
+                PAT_AGENT_LD(&a.ctl->claimed) >= (uint32_t)a.first[kSolveXcds])
+              break;
+          }
           v = __hip_atomic_fetch_or(&d->roll, kSolveClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           while (__hip_atomic_load(&d->ready, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) < v && ++spin < kSolveSpin) {
           }
@@ -434,12 +443,11 @@ __device__ __forceinline__ bool join_domain(const SolveArgs& a, SolveShared& sh,
   dm.xr = __builtin_amdgcn_readfirstlane(sh.xr);
   dm.nx = __builtin_amdgcn_readfirstlane(sh.nx);
   dm.dies = 0;
-  dm.flag = dm.d->flag;
+  dm.flag = a.doms[WHOLE ? x : (int)(dm.d - a.doms)].flag;
   if (WHOLE)
     for (int y = 0; y < kSolveXcds; ++y) {
       const int c = __builtin_amdgcn_readfirstlane((int)PAT_AGENT_LD(&dm.d->count[y]));
       if (c > 0) dm.dies |= 1u << y;
-      if (y < x) dm.flag += c;
     }
   dm.epoch = 0;
   __syncthreads();
@@ -460,6 +468,7 @@ __device__ __forceinline__ int claim_instance(const SolveArgs& a, Domain<WHOLE>&
         const uint32_t i = PAT_AGENT_ADD(&a.ctl->head[y][0], 1u);
         if (i < (uint32_t)len) got = (uint32_t)beg + i + 1;
       }
+      if (got) PAT_AGENT_ADD(&a.ctl->claimed, 1u);
       dm.sh->claim = got;
       if (dm.n > 1) PAT_AGENT_ST(&dm.d->claim, (seq << 16) | got);
     } else {

@@ -11,7 +11,12 @@ constexpr int kSolveDomains = 16;    // most domains per die
 constexpr int kSolveQueue = 32768;   // most instances of a queue (16 bits hold a claim)
 constexpr int kSolveSpin = 1 << 24;  // polls after which a wait gives up (seconds)
 constexpr uint32_t kSolveClosed = 0x80000000u;
-constexpr uint64_t kSolveRollTicks = 10000;  // of the 100 MHz clock
+// A domain whose members are held up (solves on other streams have their
+// places) waits for them rather than run without: one missing of 256 doubles
+// its time.  Solve time in ticks of the 100 MHz clock, 25 us a step; the wait
+// ends after half a second in any case (before the others give up on it).
+constexpr uint64_t kSolveRollTicks = 50000000;
+constexpr uint32_t solve_ticks(long steps) { return steps > 10000 ? 25000000u : (uint32_t)(2500 * steps); }
 
 // Grids above this run on one domain over every die, the others on one die.
 // Per step (forward, lossy, before the multipliers stayed in registers), on
@@ -43,19 +48,26 @@ constexpr int solve_members(int nx, int ny) {
 }
 
 // One domain: its roll, the instance its first member claimed, and the
-// barrier words: a flag per member, die by die, and one word per die, each on
-// a line of its own (on one line, every die's store takes it from all others:
-// 512^2 38.3 us per step, 36.0 apart).
+// barrier's words: one per die, each on a line of its own (over every die:
+// in every die's entry), and one per member, two on a line.  (Words on one line queue up at the L2 when all are stored
+// and polled at once.  Per step, the members' words 32, 8, 2 and 1 on a line:
+// 128^2 17.6, 16.2, 15.3, 15.0 us, 256^2 26.1, 24.0, 23.1, 23.5; the dies'
+// words 8 and 1 on a line: 512^2 38.3 and 36.0.)
 constexpr int kSolveLine = 32;  // words
+constexpr int kSolveFlagLines = 16;
+constexpr int solve_flag(int member) {
+  return member % kSolveFlagLines * kSolveLine + member / kSolveFlagLines;
+}
 struct alignas(128) SolveDom {
   uint32_t roll, n, claim, ready;
   uint32_t count[kSolveXcds];  // members per die (domains over every die)
   alignas(128) uint32_t lead[kSolveXcds * kSolveLine];
-  alignas(128) uint32_t flag[kSolveXcds * kSolveCus];
+  alignas(128) uint32_t flag[kSolveFlagLines * kSolveLine];  // (over every die: die x's are in the x-th entry)
 };
 struct alignas(128) SolveCtl {
   uint32_t ticket[kSolveXcds][32];  // blocks seen per die
   uint32_t head[kSolveXcds][32];    // next instance of each die's list
+  alignas(128) uint32_t claimed;    // instances taken
 };
 
 struct SolveArgs {
@@ -67,6 +79,7 @@ struct SolveArgs {
   int32_t first[kSolveXcds + 1];  // where each die's list begins
   int32_t members, domains;    // members per domain, domains per die
   int32_t s0, s1;
+  uint32_t solve_ticks;
 };
 
 constexpr size_t solve_ctl_bytes(int domains) { return sizeof(SolveCtl) + sizeof(SolveDom) * kSolveXcds * domains; }
