@@ -409,31 +409,34 @@ bool resident(const pat_plan* p) { return solve_shape(p->desc.ndim, p->hp.n[0], 
 // Whether a batch runs as resident solves: when their estimated time is below
 // that of the batched launches (microseconds, forward, lossy; measured from
 // one to 64 instances of 64^2 to 512^2).  A resident step takes
-// 13 us + 0.21 us per 1000 points on its die, the dies working side by side
-// and each holding 32 / members domains; over every die 24 us + 0.05 us per
-// 1000 points, one instance at a time.  The instances over every die and
-// those on one run side by side too, at 0.4 of the shorter part's time:
-// 512^2 (600 steps) with 256^2 (300) 25.1 ms, 23.8 ms and 8.7 ms alone.  A
+// 11.5 us + 0.17 us per 1000 points on its die, the dies working side by side
+// and each holding 32 / members domains; over every die 20.5 us + 0.053 us
+// per 1000 points, one instance at a time.  The instances over every die and
+// those on one run side by side too, at 0.4 of the shorter part's time.  A
 // step of the batched launches takes 42 us + 0.02 us per 1000 points of all
-// its instances, 54 us when they have several shapes (512^2 with 256^2 60 us,
-// 4 of 128^2 with 4 of 256^2 65 us).
+// its instances; 54 us where classes of several shapes share their launches
+// (512^2 with 256^2 60 us, 4 of 128^2 with 4 of 256^2 65 us); 30 us and more
+// for each class where they do not (8 of 256^2 with 8 of 64^2 104 us, 6 each
+// of 128^2, 128 x 64 and 64^2 91 us).
 bool resident_pays(pat_plan* const* plans, int nb) {
-  double die[kSolveXcds] = {}, whole = 0, longest = 0, work = 0, steps_max = 1;
+  double die[kSolveXcds] = {}, whole = 0, longest = 0, work = 0, steps_max = 1, steps_sum = 0;
   std::vector<double> cost;  // time on a die, by the share of it that the instance holds
-  bool one_shape = true;
+  std::map<std::tuple<int, int, int>, int> classes;
+  bool shared = true;
   if (nb > kSolveQueue) return false;
   for (int i = 0; i < nb; ++i) {
     const pat_plan* p = plans[i];
     if (!resident(p)) return false;
     const int nx = p->hp.n[0], ny = p->hp.n[1];
     const double steps = std::max(0, p->desc.nt - 1), kpts = 1e-3 * (double)p->npoints;
-    one_shape = one_shape && nx == plans[0]->hp.n[0] && ny == plans[0]->hp.n[1];
+    shared = shared && fused_size(nx) && fused_size(ny);
+    if (classes.emplace(std::make_tuple(nx, ny, (int)p->desc.nt), i).second) steps_sum += steps;
     steps_max = std::max(steps_max, steps);
     work += steps * kpts;
     if (solve_whole(nx, ny)) {
-      whole += steps * (24.0 + 0.05 * kpts);
+      whole += steps * (20.5 + 0.053 * kpts);
     } else {
-      const double t = steps * (13.0 + 0.21 * kpts);
+      const double t = steps * (11.5 + 0.17 * kpts);
       longest = std::max(longest, t);
       cost.push_back(t * solve_members(nx, ny) / kSolveCus);
     }
@@ -442,7 +445,9 @@ bool resident_pays(pat_plan* const* plans, int nb) {
   for (double c : cost) *std::min_element(die, die + kSolveXcds) += c;
   const double dies = std::max(longest, *std::max_element(die, die + kSolveXcds));
   const double t_res = std::max(whole, dies) + 0.4 * std::min(whole, dies);
-  return t_res < steps_max * (one_shape ? 42.0 : 54.0) + 0.02 * work;
+  double launches = steps_max * 42.0;
+  if (classes.size() > 1) launches = shared ? steps_max * 54.0 : std::max(launches, steps_sum * 30.0);
+  return t_res < launches + 0.02 * work;
 }
 
 SolveArgs solve_args(void* ctl, int domains) {
