@@ -197,8 +197,8 @@ __global__ void __launch_bounds__((ColGeo<NA>::NTH)) k_coly(const DevPlan* __res
 // column lives in one wavefront and its FFT exchanges need only wavefront
 // ordering, not block barriers.  Data pass between the mappings through the
 // column's LDS region (padded layout, odd column stride: conflict-free).
-// Every input a block needs is loaded before the first transform (up to two
-// fields), so that the second field's loads overlap the first's arithmetic.
+// Every input a block needs is loaded before the first transform (unless it
+// takes three fields one at a time), so that the second field's loads overlap the first's arithmetic.
 // FPB (mode 1): fields per block, taken one after another.
 template <bool WAVE>
 struct SyncOf {
@@ -219,15 +219,21 @@ struct SyncOf<true> {
 // applies both multipliers before its first inverse transform, so that only
 // the second product, not the spectrum and the multiplier operands, waits
 // in registers through it (109 VGPRs; 137 when each output was formed just
-// before its transform).  Three-field passes (3D) take their fields one at
-// a time.
+// before its transform).  The sum of three fields (3D) is bound by the chain
+// of one block: it loads and transforms all three side by side where their
+// sets fit 80 KB (up to 128 points), one at a time above.  Side by side, the
+// adjoint step takes 149.3 -> 145.1 us at 128^3 and 68.3 -> 66.4 us at 64^3.
+// The three outputs of the 3D gradient stay one at a time (side by side the
+// forward step gained 0.3 %).
 // Tiles whose two sets of regions would take more than 80 KB of LDS (512
 // points, 16 columns) transform one field at a time.
 template <int NA, int TW>
 constexpr bool col_pair_fits() { return ColGeo<NA, TW>::TILE * (NA + NA / 8 - 1) * 16 <= 81920; }
+template <int NA, int TW>
+constexpr bool col_triple_fits() { return ColGeo<NA, TW>::TILE * (NA + NA / 8 - 1) * 24 <= 81920; }
 template <int NA, int TW, int MODE, int NF, int FPB>
 constexpr int col_kf() {
-  return !col_pair_fits<NA, TW>() ? 1 : MODE == 1 ? FPB : 1;
+  return !col_pair_fits<NA, TW>() ? 1 : MODE == 1 ? FPB : MODE == 2 && NF == 3 && col_triple_fits<NA, TW>() ? 3 : 1;
 }
 template <int NA, int TW, int MODE, int NF, int FPB>
 constexpr int col_ki() {
@@ -277,7 +283,7 @@ __device__ __forceinline__ void colm_pass(const DevPlan& P, int tile_index, cons
   constexpr int KF = col_kf<NA, TW, MODE, NF, FPB>(), KI = col_ki<NA, TW, MODE, NF, FPB>();
   using Sync = typename SyncOf<(TC <= 64)>::type;
   constexpr int NIN = (MODE == 0) ? 1 : (MODE == 1 ? FPB : NF);  // input fields per block
-  constexpr bool UPFRONT = NIN <= 2;
+  constexpr bool UPFRONT = NIN <= 2 || NIN == KF;
   float2* const lds = sh.lds;
   Tw* const tws = sh.tws;
   // mapping A (memory): column ca, position ta; mapping B (transforms): column cb, lane tb
