@@ -521,7 +521,8 @@ int pat_project(int64_t n, const float* x, const float* lower, float* out, void*
 /*
  * pat_plan_sync -- wait for `plan`'s work on `stream` and report deferred
  * device errors: PAT_ENONFINITE if PAT_CHECK_FINITE was set and a non-finite
- * pressure value was produced since the last sync (the flag is then cleared).
+ * pressure value was produced since the last sync (the flag is then cleared);
+ * PAT_EHIP if a resident solve gave up waiting for its own workgroups.
  */
 int pat_plan_sync(pat_plan* plan, void* stream);
 
@@ -537,7 +538,9 @@ int pat_plan_sync(pat_plan* plan, void* stream);
  * duration [ms], the number of launches and the algorithmic bytes they moved
  * (full-grid float32 arrays each pass must read and write, per grid point,
  * times the points the launch covers).  Not thread-safe against concurrent
- * begin/end calls; launches captured into graphs are not timed.
+ * begin/end calls; launches captured into graphs are not timed.  Between begin
+ * and end every solve runs with a launch per pass (2D solves of 32 to 512
+ * points per axis are one launch otherwise).
  *
  * Forward lossy 2D sequence: 0 gradient (column), 1 velocity (row),
  * 2 divergence (column), 3 density (row), 4 absorption (column),

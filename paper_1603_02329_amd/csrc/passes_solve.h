@@ -10,7 +10,7 @@
 // owns it.  No cache is written back or invalidated between passes: an
 // agent-scope release or acquire fence costs 15-20 us with 256 workgroups
 // running (every wavefront's write-back and invalidate queue up at the L2);
-// this barrier costs 0.7-1.05 us within a die and 1.9 us over all eight.  A
+// this barrier costs about 0.6 us within a die and 1.5-1.9 us over all eight.  A
 // pass of its own launch costs 5.5-9 us at 64^2 to 512^2, whatever the grid.
 //
 // Tiles are cut for latency: four values per lane (eight for columns of 512
@@ -26,10 +26,10 @@
 // of the barrier.
 //
 // Per step of the time loop, launches, resident, and resident with these two
-// (us): lossless forward 64^2 22.5, 10.7, 9.5; lossy forward 64^2 32.9, 15.3,
-// 12.9, 128^2 36.7, 20.8, 17.7-19.4 (by die), 256 x 64 40.6, 20.0, 17.3, 256^2
-// 43.9, 28.9, 26.3, 512^2 53.7, 39.8, 35.4; the adjoint within 5% of the
-// forward.
+// and the barrier's words on lines of their own (us): lossless forward 64^2
+// 22.5, 10.7, 8.8; lossy forward 64^2 32.9, 15.3, 12.5, 128^2 36.7, 20.8,
+// 15.3, 256 x 64 40.6, 20.0, 15.0, 256^2 43.9, 28.9, 22.9, 512^2 53.7, 39.8,
+// 34.3; the adjoint within 5% of the forward.
 //
 // Membership is dynamic, so that a domain never waits for a workgroup that
 // is not running: a domain's roll is closed when it is complete or after a
