@@ -19,9 +19,9 @@ constexpr uint64_t kSolveRollTicks = 50000000;
 constexpr uint32_t solve_ticks(long steps) { return steps > 10000 ? 25000000u : (uint32_t)(2500 * steps); }
 
 // Grids above this run on one domain over every die, the others on one die.
-// Per step (forward, lossy, before the multipliers stayed in registers), on
-// one die and over all: 256^2 27.8 and 30.6 us; 512 x 128 27.0 and 29.5;
-// 512 x 256 50.2 and 31.5; 512^2 87.6 and 39.5.
+// Per step (forward, lossy), on one die and over all: 256^2 22.9 and 25.8 us;
+// 512 x 128 22.3 and 24.9; 128 x 512 24.7 and 28.5; 512 x 256 50.2 and 31.5,
+// 512^2 87.6 and 39.5 (both before the barrier's words were spread).
 constexpr int kSolveDiePoints = 65536;
 constexpr bool solve_whole(int nx, int ny) { return nx * ny > kSolveDiePoints; }
 // Rows and columns are carried by two lanes where the per-launch passes have
