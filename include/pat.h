@@ -522,9 +522,19 @@ int pat_project(int64_t n, const float* x, const float* lower, float* out, void*
  * pat_plan_sync -- wait for `plan`'s work on `stream` and report deferred
  * device errors: PAT_ENONFINITE if PAT_CHECK_FINITE was set and a non-finite
  * pressure value was produced since the last sync (the flag is then cleared);
- * PAT_EHIP if a resident solve gave up waiting for its own workgroups.
+ * PAT_EHIP if a resident solve gave up waiting for its own workgroups (a solve
+ * of 2D grids whose workgroups meet at barriers; a wait is given up after
+ * seconds).  The result of such a call, of every instance of a batch that did
+ * not come to its end, is NaN throughout, and so are the later samples of a
+ * pat_forward_range sequence.  When both happened, PAT_EHIP is reported and the
+ * finite flag stays for the next sync.
+ *
+ * pat_plan_wait_limit -- polls after which the waits of the plan's resident
+ * solves are given up; 0: the default (2^24, seconds).  Batches take the limit
+ * when they are created (the least of their plans').
  */
 int pat_plan_sync(pat_plan* plan, void* stream);
+int pat_plan_wait_limit(pat_plan* plan, int32_t polls);
 
 /*
  * Diagnostics: HIP-event timing of one pass of the time step.

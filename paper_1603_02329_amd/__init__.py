@@ -39,7 +39,7 @@ EXPORTED = [
     "pat_dot_f64", "pat_residual_f64", "pat_residual_f64_batched", "pat_residual_batched_work_bytes", "pat_plan_sync", "pat_strerror", "pat_timing_begin",
     "pat_timing_end", "pat_batch_autotune", "pat_tuning_report", "pat_batch_set_tile", "pat_batch_time_pass",
     "pat_tv_smooth", "pat_restrict_lower", "pat_axpby", "pat_project", "pat_forward_batched",
-    "pat_adjoint_batched", "pat_desc_check", "pat_tv_prox_noalloc", "pat_diag_sync_costs",
+    "pat_adjoint_batched", "pat_desc_check", "pat_tv_prox_noalloc", "pat_diag_sync_costs", "pat_plan_wait_limit",
 ]
 
 
@@ -110,6 +110,7 @@ def lib() -> ctypes.CDLL:
         "pat_residual_f64_batched": (ctypes.c_int, [i32, vp, vp, vp, vp, vp, vp, vp]),
         "pat_residual_batched_work_bytes": (ctypes.c_size_t, [i32]),
         "pat_plan_sync": (ctypes.c_int, [vp, vp]),
+        "pat_plan_wait_limit": (ctypes.c_int, [vp, i32]),
         "pat_strerror": (ctypes.c_char_p, [ctypes.c_int]),
         "pat_timing_begin": (ctypes.c_int, [i32, i32, i32]),
         "pat_timing_end": (ctypes.c_int, [ctypes.POINTER(f64), ctypes.POINTER(i64), ctypes.POINTER(f64)]),
@@ -285,8 +286,15 @@ class Plan:
         return data
 
     def sync(self):
-        """Wait for the plan's work; raises PatError(ENONFINITE) if flagged."""
+        """Wait for the plan's work; raises PatError, PAT_EHIP if a resident
+        solve gave up (its results are NaN) and PAT_ENONFINITE if a non-finite
+        pressure was flagged."""
         _check(lib().pat_plan_sync(self._h, _stream()), "pat_plan_sync")
+
+    def wait_limit(self, polls: int) -> None:
+        """Polls after which a resident solve's waits are given up (0: the
+        default; see pat_plan_wait_limit)."""
+        _check(lib().pat_plan_wait_limit(self._h, int(polls)), "pat_plan_wait_limit")
 
 
 class Batch:

@@ -152,9 +152,10 @@ struct TimeScope {
   }
 };
 
-__global__ void k_set_io(DevPlan* p, const float* in, float* out) {
+__global__ void k_set_io(DevPlan* p, int32_t* bad, const float* in, float* out) {
   p->in = in;
   p->out = out;
+  bad[kBadOpen] = 0;
 }
 
 constexpr int kIoMax = 64;
@@ -168,6 +169,7 @@ __global__ void k_set_io_many(DevPlan* recs, int nb, IoArgs a) {
   if (i < nb) {
     recs[i].in = a.in[i];
     recs[i].out = a.out[i];
+    recs[i].bad[kBadOpen] = 0;
   }
 }
 // W^T h of every sample, one sum per node group of the scatter operator (a
@@ -386,7 +388,7 @@ Runner eager_runner(const pat_plan* p) {
 }
 
 int set_io(const pat_plan* p, const float* in, float* out, hipStream_t st) {
-  hipLaunchKernelGGL(k_set_io, dim3(1), dim3(1), 0, st, p->dp, in, out);
+  hipLaunchKernelGGL(k_set_io, dim3(1), dim3(1), 0, st, p->dp, p->hp.bad, in, out);
   return hipGetLastError() == hipSuccess ? PAT_OK : PAT_EHIP;
 }
 
@@ -470,7 +472,9 @@ int solve_one(const pat_plan* p, int dir, int s0, int s1, hipStream_t st) {
   a.s0 = s0;
   a.s1 = s1;
   a.solve_ticks = solve_ticks(s1 - s0);
-  return launch_solve(p->hp.n[0], p->hp.n[1], dir, p->lossy, a, st) == hipSuccess ? PAT_OK : PAT_EHIP;
+  a.polls = p->polls ? p->polls : kSolveSpin;
+  return launch_solve(p->hp.n[0], p->hp.n[1], dir, p->lossy, a, p->hp.bad + kBadOpen, st) == hipSuccess ? PAT_OK
+                                                                                                        : PAT_EHIP;
 }
 
 // the time loop of one plan: steps [s0, s1) of direction dir
@@ -690,6 +694,7 @@ struct pat_batch {
     int first[kSolveXcds + 1] = {};
     int members = 0, domains = 0;
     long steps = 0;  // of its longest instance
+    int polls = kSolveSpin;  // the least of its plans' limits
   };
   bool resident = false;
   std::vector<Queue> queue;
@@ -843,10 +848,11 @@ int batch_run_resident(pat_batch* b, int dir, const float* const* in, float* con
     a.list = q.list;
     a.members = q.members;
     a.solve_ticks = solve_ticks(q.steps);
+    a.polls = q.polls;
     for (int x = 0; x <= kSolveXcds; ++x) a.first[x] = q.first[x];
     hipStream_t s = k == 0 ? st : b->lanes[(k - 1) % b->lanes.size()];
     if (k > 0 && hipStreamWaitEvent(s, b->fork, 0) != hipSuccess) return PAT_EHIP;
-    if (launch_solve(q.nx, q.ny, dir, q.lossy, a, s) != hipSuccess) return PAT_EHIP;
+    if (launch_solve(q.nx, q.ny, dir, q.lossy, a, nullptr, s) != hipSuccess) return PAT_EHIP;
   }
   for (size_t k = 0; nq > 1 && k < std::min(nq - 1, b->lanes.size()); ++k) {
     if (hipEventRecord(b->lead, b->lanes[k]) != hipSuccess || hipStreamWaitEvent(st, b->lead, 0) != hipSuccess)
@@ -1160,7 +1166,9 @@ extern "C" int pat_batch_create_ex(pat_batch** out, pat_plan* const* plans, int3
       auto& q = b->queue.back();
       std::tie(q.nx, q.ny, q.lossy) = sh.first;
       for (const auto& w : work) {
-        q.steps = std::max(q.steps, (long)b->cls[w.k].plans[w.i]->desc.nt - 1);
+        const pat_plan* p = b->cls[w.k].plans[w.i];
+        q.steps = std::max(q.steps, (long)p->desc.nt - 1);
+        if (p->polls) q.polls = std::min(q.polls, (int)p->polls);
         const int x = (int)(std::min_element(load, load + kSolveXcds) - load);
         q.order[x].emplace_back(w.k, w.i);
         load[x] += w.w;

@@ -196,7 +196,14 @@ __device__ __forceinline__ void absorption_coefs(const DevPlan& P, const float2 
 }
 
 __device__ __forceinline__ void check_finite(const DevPlan& P, float2 v) {
-  if ((P.flags & PAT_CHECK_FINITE) && !(isfinite(v.x) && isfinite(v.y))) atomicOr(P.bad, 1);
+  if ((P.flags & PAT_CHECK_FINITE) && !(isfinite(v.x) && isfinite(v.y))) atomicOr(P.bad + kBadFlags, kFlagNonFinite);
+}
+
+// whether the resident solve before this pass gave up (the flag is raised then)
+__device__ __forceinline__ bool unfinished(const DevPlan& P) {
+  const bool open = gld(P.bad, kBadOpen) != 0;
+  if (open && threadIdx.x == 0) atomicOr(P.bad + kBadFlags, kFlagGaveUp);
+  return open;
 }
 
 // ------------------------------------------------------------------ row passes
@@ -734,7 +741,9 @@ __device__ __forceinline__ void row_pass(const DevPlan& P, int tile, int it, flo
     r2c<N>(x, P.S[1] + io.base, L, t, valid, tws);
   } else if constexpr (K == R_ADJ_FINAL || K == R_ADJ_SCATTER_ONLY) {
     float2 v[E], rs[E], ic[E];
+    bool open = false;
     if constexpr (K == R_ADJ_FINAL) {
+      open = unfinished(P);
       io.ld(P.S[0], v);
       io.ld(P.r[0], rs);
 #pragma unroll
@@ -758,6 +767,12 @@ __device__ __forceinline__ void row_pass(const DevPlan& P, int tile, int it, flo
     for (int m = 0; m < E; ++m) {
       v[m] = L[t + T * m];
       if constexpr (K == R_ADJ_FINAL) v[m] = v[m] + mul2(rs[m], ic[m]);
+    }
+    if constexpr (K == R_ADJ_FINAL) {
+      if (open) {
+#pragma unroll
+        for (int m = 0; m < E; ++m) v[m] = f2(NAN, NAN);
+      }
     }
     io.st(P.out, v);
   }

@@ -19,7 +19,8 @@ __global__ void __launch_bounds__(RowGeo<N>::NTH) k_row(const DevPlan* __restric
 
 // ------------------------------------------------------------------ gather reduction
 // data[n][s] = sum of the sensor's partial row sums, for samples n0 <= n < n1
-// (n1 <= 0 selects nt)
+// (n1 <= 0 selects nt).  After a resident solve that gave up: NaN, and a
+// state from which every later sample is NaN too.
 __global__ void __launch_bounds__(256) k_reduce(const DevPlan* __restrict__ plans, const int2* __restrict__ table,
                                                 int n0, int n1) {
   const int2 job = table ? table[blockIdx.x] : make_int2(0, (int)blockIdx.x);
@@ -30,6 +31,11 @@ __global__ void __launch_bounds__(256) k_reduce(const DevPlan* __restrict__ plan
   if (idx >= total) return;
   const int n = (int)(idx / P.ns);
   const int s = (int)(idx - (long)n * P.ns);
+  if (unfinished(P)) {
+    if (job.y == 0 && threadIdx.x == 0) P.S[0][0] = f2(NAN, NAN);
+    gst(P.out, idx, NAN);
+    return;
+  }
   const float* part = P.partial + (long)n * P.nslots;
   const int k0 = gld(P.slot_ptr, s), k1 = gld(P.slot_ptr, s + 1);
   float acc = gld(part, k0);

@@ -34,7 +34,9 @@
 // Membership is dynamic, so that a domain never waits for a workgroup that
 // is not running: a domain's roll is closed when it is complete or after a
 // bounded time, and a workgroup that comes later leaves at once.  Every
-// member is then resident until the queue is empty.  Every wait is bounded.
+// member is then resident until the queue is empty.  Every wait is bounded; a
+// member whose wait runs out leaves, and every instance that not all members
+// of a domain took to its end, begun or not, stays marked (kSolveOpen).
 #pragma once
 
 #include <type_traits>
@@ -314,7 +316,8 @@ struct SolveGeo {
 };
 
 struct SolveShared {
-  int fail, rank, n, xr, nx;
+  uint32_t fail;  // barrier at which a wait ran out (0: none)
+  int rank, n, xr, nx;
   uint32_t claim;
 };
 template <int NX, int NY>
@@ -341,6 +344,7 @@ struct Domain {
   uint32_t* flag; // the flags of this die's members
   uint32_t dies;  // dies with members
   uint32_t epoch;
+  int polls;      // left to a wait; 0 once one ran out
 
   __device__ __forceinline__ static bool reached(const uint32_t* w, uint32_t epoch) {
     return (int32_t)(PAT_AGENT_LD(w) - epoch) >= 0;
@@ -380,12 +384,20 @@ struct Domain {
   // until every lane's word has reached this barrier; marks the block when that never happens
   __device__ __forceinline__ void poll(const uint32_t* w) {
     int spin = 0;
-    while (!__all(reached(w, epoch)) && ++spin < kSolveSpin) {
+    while (!__all(reached(w, epoch)) && ++spin < polls) {
     }
-    if (spin >= kSolveSpin && (threadIdx.x & 63) == 0) sh->fail = 1;
+    if (spin >= polls) {
+      if (polls != 0 && (threadIdx.x & 63) == 0) sh->fail = epoch;
+      polls = 0;
+    }
   }
-  // whether a wait of this block has run out
-  __device__ __forceinline__ bool failed() const { return n > 1 && __builtin_amdgcn_readfirstlane(sh->fail) != 0; }
+  // Whether a wait of this block ran out before the last arrive(), whose
+  // block barrier makes every wavefront see it alike (one that runs out
+  // meanwhile in the first wavefront carries the current epoch).
+  __device__ __forceinline__ bool failed() const {
+    const uint32_t f = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh->fail);
+    return f != 0 && (int32_t)(f - epoch) < 0;
+  }
 };
 
 // Joins a domain of this block's die (WHOLE: the one domain); false for a
@@ -394,7 +406,7 @@ template <int WHOLE>
 __device__ __forceinline__ bool join_domain(const SolveArgs& a, SolveShared& sh, Domain<WHOLE>& dm) {
   const int x = (int)(__builtin_amdgcn_s_getreg(20 | (31 << 11)) & (kSolveXcds - 1));  // XCC_ID
   if (threadIdx.x == 0) {
-    sh.fail = 0;
+    sh.fail = 0u;
     sh.n = 0;
     const uint32_t ticket = PAT_AGENT_ADD(&a.ctl->ticket[WHOLE ? 0 : x][0], 1u);
     const int k = (int)(ticket / (uint32_t)a.members);
@@ -420,12 +432,15 @@ __device__ __forceinline__ bool join_domain(const SolveArgs& a, SolveShared& sh,
               break;
           }
           v = __hip_atomic_fetch_or(&d->roll, kSolveClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          while (__hip_atomic_load(&d->ready, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) < v && ++spin < kSolveSpin) {
+          while (__hip_atomic_load(&d->ready, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) < v && ++spin < a.polls) {
           }
-          PAT_AGENT_ST(&d->n, v);
+          // (a member that has not counted itself yet: the domain does not start)
+          if (spin >= a.polls) v = 0;
+          PAT_AGENT_ST(&d->n, v ? v : kSolveClosed);
         } else {
-          while (!(v = PAT_AGENT_LD(&d->n)) && ++spin < kSolveSpin) {
+          while (!(v = PAT_AGENT_LD(&d->n)) && ++spin < a.polls) {
           }
+          if (v == kSolveClosed) v = 0;
         }
         sh.n = (int)v;  // 0: gave up
         sh.nx = WHOLE ? (int)PAT_AGENT_LD(&d->count[x]) : (int)v;
@@ -450,6 +465,7 @@ __device__ __forceinline__ bool join_domain(const SolveArgs& a, SolveShared& sh,
       if (c > 0) dm.dies |= 1u << y;
     }
   dm.epoch = 0;
+  dm.polls = a.polls;
   __syncthreads();
   return true;
 }
@@ -475,7 +491,7 @@ __device__ __forceinline__ int claim_instance(const SolveArgs& a, Domain<WHOLE>&
       int spin = 0;
       uint32_t v;
       while (((v = PAT_AGENT_LD(&dm.d->claim)) >> 16) != (seq & 0xffffu))
-        if (++spin > kSolveSpin) {
+        if (++spin > a.polls) {
           v = 0;
           break;
         }
@@ -1011,11 +1027,6 @@ __device__ __forceinline__ void solve_col(const DevPlan& P, Domain<solve_whole(N
   }
 }
 
-// a wait ran out: the plan is marked (pat_plan_sync reports it)
-__device__ __forceinline__ void give_up(const DevPlan& P) {
-  if (threadIdx.x == 0) atomicOr(P.bad, 2);
-}
-
 // ---------------------------------------------------------------- the kernel
 // Steps [s0, s1) (s1 < 0: to the last) of direction DIR of every queued
 // instance, between the launches of the initial and the final pass.  At most
@@ -1077,8 +1088,9 @@ __global__ void __launch_bounds__((SolveGeo<NX, NY>::NTH), 3) k_solve(SolveArgs 
         solve_col<NX, NY, 2, F_B>(P, dm, sh, mb);
         dm.arrive();
       }
-      if (dm.failed()) return give_up(P);
+      if (dm.failed()) return;
     }
+    if (threadIdx.x == 0) PAT_AGENT_ADD((uint32_t*)P.bad + kBadOpen, solve_share(dm.rank, dm.n));
   }
 }
 

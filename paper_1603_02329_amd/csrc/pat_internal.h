@@ -28,6 +28,13 @@ struct alignas(16) Tw {
   float hr, hi, lr, li;
 };
 
+// Words of DevPlan::bad.  kBadFlags: what pat_plan_sync reports.  kBadOpen:
+// nonzero while a resident solve (solve.h) has not run to its end; cleared by
+// every call before its first pass and read by the pass that forms the result,
+// which is then NaN.
+constexpr int kBadFlags = 0, kBadOpen = 1, kBadWords = 2;
+constexpr int32_t kFlagNonFinite = 1, kFlagGaveUp = 2;
+
 // Everything one instance needs on the device.  Arrays are float32,
 // row-major with x fastest; "packed spectra" hold per row nx/2 complex
 // values of the x-transform, with bin 0 carrying (X[0], X[nx/2]) -- both real.
@@ -81,7 +88,7 @@ struct DevPlan {
   int32_t ngroups;          // node groups of the scatter operator
   const int32_t* slot_ptr;  // [ns + 1]
   float* partial;           // [nt][nslots]
-  int32_t* bad;             // non-finite flag (PAT_CHECK_FINITE)
+  int32_t* bad;             // [kBadFlags], [kBadOpen]
 
   // per-call I/O pointers (set by the executor before launching)
   const float* in;   // p0 (forward) or data (adjoint)
@@ -255,4 +262,5 @@ struct pat_plan {
   size_t arena_bytes = 0;
   size_t state_bytes = 0;
   void* solve = nullptr;        // control block of the resident solve (solve.h), one domain per die
+  int32_t polls = 0;            // polls after which its waits give up (0: solve.h's)
 };

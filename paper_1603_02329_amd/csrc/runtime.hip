@@ -168,7 +168,7 @@ extern "C" int pat_plan_create(pat_plan** out, const pat_desc* desc, const float
   const size_t o_sc = cv.take<float>(std::max<size_t>(1, (size_t)d.nt * so.s_grp.size()));
   const size_t o_slot = cv.take<int32_t>(so.slot_ptr.size());
   const size_t o_part = cv.take<float>((size_t)d.nt * so.nslots);
-  const size_t o_bad = cv.take<int32_t>(1);
+  const size_t o_bad = cv.take<int32_t>(kBadWords);
   const size_t o_rec = cv.take<DevPlan>(1);
   const size_t o_solve = cv.take<char>(solve_ctl_bytes(1));
   p->arena_bytes = (cv.off + 255) & ~size_t(255);
@@ -260,7 +260,7 @@ extern "C" int pat_plan_create(pat_plan** out, const pat_desc* desc, const float
   if (!rc) rc = up(o_sgrp, so.s_grp.data(), so.s_grp.size() * sizeof(SGroup));
   if (!rc) rc = up(o_stap, so.s_tap.data(), so.s_tap.size() * sizeof(STap));
   if (!rc) rc = up(o_slot, so.slot_ptr.data(), so.slot_ptr.size() * 4);
-  if (!rc && hipMemsetAsync(A + o_bad, 0, 4, st) != hipSuccess) rc = PAT_EHIP;
+  if (!rc && hipMemsetAsync(A + o_bad, 0, 4 * kBadWords, st) != hipSuccess) rc = PAT_EHIP;
 
   DevPlan& h = p->hp;
   h.ndim = nd;
@@ -359,12 +359,18 @@ extern "C" int pat_plan_info(const pat_plan* p, pat_info* info) {
 extern "C" int pat_plan_sync(pat_plan* p, void* stream) {
   if (!p) return PAT_EINVAL;
   if (hipStreamSynchronize((hipStream_t)stream) != hipSuccess) return PAT_EHIP;
-  int32_t bad = 0;
-  if (hipMemcpy(&bad, p->hp.bad, 4, hipMemcpyDeviceToHost) != hipSuccess) return PAT_EHIP;
-  if (bad) {
-    if (hipMemset(p->hp.bad, 0, 4) != hipSuccess) return PAT_EHIP;
-    return (bad & 2) ? PAT_EHIP : PAT_ENONFINITE;  // 2: a resident solve gave up waiting
-  }
+  int32_t flags = 0;
+  if (hipMemcpy(&flags, p->hp.bad + kBadFlags, 4, hipMemcpyDeviceToHost) != hipSuccess) return PAT_EHIP;
+  if (!flags) return PAT_OK;
+  // one condition a call: the flag that is not reported stays for the next
+  const int32_t told = flags & kFlagGaveUp ? kFlagGaveUp : flags, rest = flags & ~told;
+  if (hipMemcpy(p->hp.bad + kBadFlags, &rest, 4, hipMemcpyHostToDevice) != hipSuccess) return PAT_EHIP;
+  return told == kFlagGaveUp ? PAT_EHIP : PAT_ENONFINITE;
+}
+
+extern "C" int pat_plan_wait_limit(pat_plan* p, int32_t polls) {
+  if (!p || polls < 0) return PAT_EINVAL;
+  p->polls = polls;
   return PAT_OK;
 }
 

@@ -9,7 +9,7 @@ constexpr int kSolveXcds = 8;        // MI355X: 8 accelerator complex dies (XCDs
 constexpr int kSolveCus = 32;        // compute units per die
 constexpr int kSolveDomains = 16;    // most domains per die
 constexpr int kSolveQueue = 32768;   // most instances of a queue (16 bits hold a claim)
-constexpr int kSolveSpin = 1 << 24;  // polls after which a wait gives up (seconds)
+constexpr int kSolveSpin = 1 << 24;  // polls after which a wait gives up (seconds), if not set otherwise
 constexpr uint32_t kSolveClosed = 0x80000000u;
 // A domain whose members are held up (solves on other streams have their
 // places) waits for them rather than run without: one missing of 256 doubles
@@ -80,7 +80,14 @@ struct SolveArgs {
   int32_t members, domains;    // members per domain, domains per die
   int32_t s0, s1;
   uint32_t solve_ticks;
+  int32_t polls;               // polls after which a wait gives up
 };
+
+// The kBadOpen word of an instance: set before the queue starts, then each of
+// the n members of its domain adds its share once its own part of the time
+// loop is done.  Zero again only if all of them came to the end.
+constexpr uint32_t kSolveOpen = 0x10000;
+constexpr uint32_t solve_share(int rank, int n) { return rank == 0 ? 0u - kSolveOpen - (uint32_t)(n - 1) : 1u; }
 
 constexpr size_t solve_ctl_bytes(int domains) { return sizeof(SolveCtl) + sizeof(SolveDom) * kSolveXcds * domains; }
 
@@ -88,7 +95,9 @@ constexpr size_t solve_ctl_bytes(int domains) { return sizeof(SolveCtl) + sizeof
 inline bool solve_shape(int ndim, int nx, int ny) {
   return ndim == 2 && nx >= 32 && nx <= 512 && ny >= 32 && ny <= 512;
 }
-// clears the control block and runs the queue's time loops, all of one shape
-hipError_t launch_solve(int nx, int ny, int dir, int lossy, SolveArgs a, hipStream_t st);
+// clears the control block, marks the instances as open (open: the kBadOpen
+// word of the one instance when there is no list) and runs the queue's time
+// loops, all of one shape
+hipError_t launch_solve(int nx, int ny, int dir, int lossy, SolveArgs a, int32_t* open, hipStream_t st);
 
 }  // namespace pat
