@@ -529,11 +529,16 @@ int pat_project(int64_t n, const float* x, const float* lower, float* out, void*
  * pat_forward_range sequence.  When both happened, PAT_EHIP is reported and the
  * finite flag stays for the next sync.
  *
+ * pat_solves_check -- wait for `stream` and report PAT_EHIP if a resident solve
+ * of any of the `count` plans gave up since the last check or sync; that flag is
+ * then cleared in all of them.  The finite flags are left alone.
+ *
  * pat_plan_wait_limit -- polls after which the waits of the plan's resident
  * solves are given up; 0: the default (2^24, seconds).  Batches take the limit
  * when they are created (the least of their plans').
  */
 int pat_plan_sync(pat_plan* plan, void* stream);
+int pat_solves_check(pat_plan* const* plans, int32_t count, void* stream);
 int pat_plan_wait_limit(pat_plan* plan, int32_t polls);
 
 /*

@@ -17,7 +17,7 @@ import numpy as np
 
 __all__ = ["lib", "PatError", "Plan", "Batch", "tv_prox", "restrict", "prolong", "dot_f64", "residual_f64", "residual_f64_batched",
            "tv_smooth", "restrict_lower", "axpby", "project", "tv_prox_batched", "forward_batched",
-           "adjoint_batched",
+           "adjoint_batched", "solves_check",
            "LIB_PATH", "EXPORTED"]
 
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libpat.so")
@@ -39,7 +39,8 @@ EXPORTED = [
     "pat_dot_f64", "pat_residual_f64", "pat_residual_f64_batched", "pat_residual_batched_work_bytes", "pat_plan_sync", "pat_strerror", "pat_timing_begin",
     "pat_timing_end", "pat_batch_autotune", "pat_tuning_report", "pat_batch_set_tile", "pat_batch_time_pass",
     "pat_tv_smooth", "pat_restrict_lower", "pat_axpby", "pat_project", "pat_forward_batched",
-    "pat_adjoint_batched", "pat_desc_check", "pat_tv_prox_noalloc", "pat_diag_sync_costs", "pat_plan_wait_limit",
+    "pat_adjoint_batched", "pat_desc_check", "pat_tv_prox_noalloc", "pat_diag_sync_costs", "pat_solves_check",
+    "pat_plan_wait_limit",
 ]
 
 
@@ -110,6 +111,7 @@ def lib() -> ctypes.CDLL:
         "pat_residual_f64_batched": (ctypes.c_int, [i32, vp, vp, vp, vp, vp, vp, vp]),
         "pat_residual_batched_work_bytes": (ctypes.c_size_t, [i32]),
         "pat_plan_sync": (ctypes.c_int, [vp, vp]),
+        "pat_solves_check": (ctypes.c_int, [pp, i32, vp]),
         "pat_plan_wait_limit": (ctypes.c_int, [vp, i32]),
         "pat_strerror": (ctypes.c_char_p, [ctypes.c_int]),
         "pat_timing_begin": (ctypes.c_int, [i32, i32, i32]),
@@ -428,6 +430,13 @@ def _grid3(plan) -> list:
 def _arch() -> str:
     torch = _torch()
     return str(torch.cuda.get_device_properties(torch.cuda.current_device()).gcnArchName).split(":")[0]
+
+
+def solves_check(plans: Sequence[Plan]) -> None:
+    """Wait for the current stream; raises PatError(PAT_EHIP) if a resident
+    solve of one of the plans gave up (see pat_solves_check)."""
+    hs = (ctypes.c_void_p * len(plans))(*[p.handle.value for p in plans])
+    _check(lib().pat_solves_check(hs, len(plans), _stream()), "pat_solves_check")
 
 
 def timing_begin(direction: int, pass_index: int, nx: int = 0) -> None:

@@ -31,8 +31,8 @@ struct alignas(16) Tw {
 // Words of DevPlan::bad.  kBadFlags: what pat_plan_sync reports.  kBadOpen:
 // nonzero while a resident solve (solve.h) has not run to its end; cleared by
 // every call before its first pass and read by the pass that forms the result,
-// which is then NaN.
-constexpr int kBadFlags = 0, kBadOpen = 1, kBadWords = 2;
+// which is then NaN.  kBadAny: scratch of pat_solves_check.
+constexpr int kBadFlags = 0, kBadOpen = 1, kBadAny = 2, kBadWords = 3;
 constexpr int32_t kFlagNonFinite = 1, kFlagGaveUp = 2;
 
 // Everything one instance needs on the device.  Arrays are float32,
@@ -88,7 +88,7 @@ struct DevPlan {
   int32_t ngroups;          // node groups of the scatter operator
   const int32_t* slot_ptr;  // [ns + 1]
   float* partial;           // [nt][nslots]
-  int32_t* bad;             // [kBadFlags], [kBadOpen]
+  int32_t* bad;             // [kBadFlags], [kBadOpen], [kBadAny]
 
   // per-call I/O pointers (set by the executor before launching)
   const float* in;   // p0 (forward) or data (adjoint)

@@ -368,6 +368,42 @@ extern "C" int pat_plan_sync(pat_plan* p, void* stream) {
   return told == kFlagGaveUp ? PAT_EHIP : PAT_ENONFINITE;
 }
 
+namespace {
+constexpr int kCheckMax = 64;
+struct CheckArgs {
+  int32_t* bad[kCheckMax];
+};
+// any <- 1 if a plan's solve gave up (that flag is cleared)
+__global__ void k_solves_check(CheckArgs a, int n, int32_t* any) {
+  const int i = threadIdx.x;
+  if (i < n && (atomicAnd(a.bad[i] + kBadFlags, ~kFlagGaveUp) & kFlagGaveUp)) atomicOr(any, 1);
+}
+__global__ void k_clear_word(int32_t* w) { *w = 0; }
+}  // namespace
+
+extern "C" int pat_solves_check(pat_plan* const* plans, int32_t count, void* stream) {
+  if (count < 0 || (count > 0 && !plans)) return PAT_EINVAL;
+  for (int i = 0; i < count; ++i)
+    if (!plans[i]) return PAT_EINVAL;
+  hipStream_t st = (hipStream_t)stream;
+  if (count > 0) {
+    int32_t* any = plans[0]->hp.bad + kBadAny;
+    hipLaunchKernelGGL(k_clear_word, dim3(1), dim3(1), 0, st, any);
+    for (int i0 = 0; i0 < count; i0 += kCheckMax) {
+      CheckArgs a{};
+      const int n = std::min(kCheckMax, count - i0);
+      for (int i = 0; i < n; ++i) a.bad[i] = plans[i0 + i]->hp.bad;
+      hipLaunchKernelGGL(k_solves_check, dim3(1), dim3(kCheckMax), 0, st, a, n, any);
+    }
+    int32_t told = 0;
+    if (hipGetLastError() != hipSuccess || hipMemcpyAsync(&told, any, 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
+        hipStreamSynchronize(st) != hipSuccess)
+      return PAT_EHIP;
+    if (told) return PAT_EHIP;
+  }
+  return PAT_OK;
+}
+
 extern "C" int pat_plan_wait_limit(pat_plan* p, int32_t polls) {
   if (!p || polls < 0) return PAT_EINVAL;
   p->polls = polls;

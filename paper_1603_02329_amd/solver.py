@@ -31,7 +31,7 @@ import math
 from dataclasses import dataclass
 from typing import List, Optional
 
-from . import Batch, Plan, axpby, dot_f64, project, prolong, residual_f64, restrict, restrict_lower, tv_prox, tv_smooth
+from . import Batch, Plan, axpby, dot_f64, project, prolong, residual_f64, restrict, restrict_lower, solves_check, tv_prox, tv_smooth
 
 __all__ = ["Level", "MGParams", "MGRecord", "IterState", "save_state", "load_state", "power_iteration", "fista",
            "fista_batched", "coarse_fista", "coarse_mg", "mg_fista"]
@@ -61,8 +61,12 @@ class Level:
         return half, self.adjoint(r)
 
     def value_f(self, x) -> float:
-        """f(x) alone (one forward solve)."""
-        return residual_f64(self.forward(x), self.data)[1]
+        """f(x) alone (one forward solve).  Every iteration ends in one: here,
+        where the host waits anyway, a solve of the plan that gave up raises
+        (the prox and the projections would turn its NaN into zeros)."""
+        half = residual_f64(self.forward(x), self.data)[1]
+        solves_check([self.plan])
+        return half
 
     def objective(self, x) -> float:
         """F(x) = f(x) + lam TV(x); keeps the residual norm RES(x) =
@@ -87,6 +91,7 @@ def power_iteration(plan: Plan, v0, n_iter: int = 30) -> float:
         w = plan.adjoint(plan.forward(v))
         lam = math.sqrt(dot_f64(w))
         v = axpby(1.0 / lam, w, 0.0, w)
+    solves_check([plan])
     return lam
 
 
@@ -193,6 +198,7 @@ def fista_batched(levels, x0s, n_iter: int, momentum: bool = True, prox_iter: in
             xs = tv_prox_batched(zs, [lv.alpha * lv.lam for lv in levels], prox_iter)
             dx = batch.forward(xs)
             halves = [residual_f64(di, lv.data)[1] for di, lv in zip(dx, levels)]
+            solves_check([lv.plan for lv in levels])
             Fs = [h + lv.lam * tv_smooth(x, 0.0) for h, lv, x in zip(halves, levels, xs)]
             for lv, h in zip(levels, halves):
                 lv.res = math.sqrt(2.0 * h)

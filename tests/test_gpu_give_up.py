@@ -1,6 +1,7 @@
 """GPU: a resident solve whose workgroups give up waiting for each other (here
 after one poll, set from the host; every workgroup still ends normally) shows:
-its results are NaN throughout, the plan says so once, and instances of a batch's queue that were never begun are reported like the rest."""
+its results are NaN throughout, the plan says so once, the solver raises, and
+instances of a batch's queue that were never begun are reported like the rest."""
 import numpy as np
 import pytest
 
@@ -10,6 +11,7 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 import paper_1603_02329_amd as pat  # noqa: E402
+from paper_1603_02329_amd import solver  # noqa: E402
 
 DEV = "cuda"
 
@@ -39,7 +41,9 @@ def test_given_up_solve_is_nan_and_reported(n, lossy):
     assert torch.isnan(plan.forward(p0)).all()
     _raises_once(plan)
     assert torch.isnan(plan.adjoint(h)).all()
-    _raises_once(plan)
+    with pytest.raises(pat.PatError):
+        pat.solves_check([plan])
+    pat.solves_check([plan])
     plan.wait_limit(0)
     assert torch.equal(plan.forward(p0), ref_d) and torch.equal(plan.adjoint(h), ref_i)
     plan.sync()
@@ -114,4 +118,23 @@ def test_batch_reports_every_instance_of_its_queue():
             _raises_once(p)
         for p in plans[2:]:
             p.sync()
+    b.forward(list(p0))
+    with pytest.raises(pat.PatError) as e:
+        pat.solves_check(list(plans))
+    assert e.value.code == pat.PAT_EHIP
+    pat.solves_check(list(plans))
     b.close()
+
+
+@pytest.mark.parametrize("run", ["fista", "batched", "power"])
+def test_solver_raises(run):
+    plan, p0, h = _case(30, n=(64, 64), nt=9, ns=7, pml=6, lossy=True)
+    level = solver.Level(plan, h, 1e-3, 0.05)
+    plan.wait_limit(1)
+    with pytest.raises(pat.PatError):
+        if run == "fista":
+            solver.fista(level, p0, 2)
+        elif run == "batched":
+            solver.fista_batched([level], [p0], 2)
+        else:
+            solver.power_iteration(plan, p0, 2)
