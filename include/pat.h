@@ -233,12 +233,17 @@ int pat_adjoint_atd(pat_plan* plan, const float* data, float* img, void* stream)
  * Batched execution of many plans (uneven sizes and nt allowed: instances
  * retire when their own time axis ends).  Each pass of the scheme runs as one
  * launch over a work table that holds the tiles of every active instance; the
- * time loop is captured into HIP graphs of `chunk` steps and replayed.
+ * time loop is captured into HIP graphs of `chunk` steps and replayed.  A batch
+ * of 2D grids of 32 to 512 points per axis that is created with the default
+ * settings (every option 0) runs its time loops as resident solves instead,
+ * side by side, where their estimated time is lower; any explicit setting,
+ * chunk = 64 too, asks for the launches it describes.
  * The plans must outlive the batch; a batch is used by one stream at a time.
  *
  *  pat_batch_create   plans: host array of nb plan pointers; chunk >= 1
  *                     (0 selects the default, 64).  All plans must have the
  *                     same ndim.
+ *  pat_batch_resident *yes = 1 if the batch runs as resident solves, else 0.
  *  pat_batch_forward  p0[i], data[i]: host arrays of nb device pointers.
  *  pat_batch_adjoint  data[i], img[i]: host arrays of nb device pointers.
  *
@@ -277,6 +282,7 @@ int pat_batch_create(pat_batch** out, pat_plan* const* plans, int32_t nb, int32_
  */
 int pat_batch_create_ex(pat_batch** out, pat_plan* const* plans, int32_t nb, int32_t chunk, int32_t parts,
                         int32_t lanes, uint32_t flags);
+int pat_batch_resident(const pat_batch* batch, int32_t* yes);
 void pat_batch_destroy(pat_batch* batch);
 int pat_batch_forward(pat_batch* batch, const float* const* p0, float* const* data, void* stream);
 int pat_batch_adjoint(pat_batch* batch, const float* const* data, float* const* img, void* stream);
@@ -320,7 +326,8 @@ int pat_adjoint_batched(pat_plan* const* plans, int32_t nb, const float* const* 
  * runs at least 0.5 % faster; the policy kept is used from then on.
  * Results stay bitwise equal to
  * pat_forward / pat_adjoint: a variant only changes how columns and fields
- * are grouped into workgroups.
+ * are grouped into workgroups.  A batch that runs as resident solves has no
+ * such passes: nothing is timed and the report is empty.
  *
  *  pat_batch_autotune  reps >= 1 timed launches per candidate.  Waits for the
  *                      batch and `stream` to be idle, runs on `stream`,

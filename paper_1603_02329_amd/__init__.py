@@ -40,7 +40,7 @@ EXPORTED = [
     "pat_timing_end", "pat_batch_autotune", "pat_tuning_report", "pat_batch_set_tile", "pat_batch_time_pass",
     "pat_tv_smooth", "pat_restrict_lower", "pat_axpby", "pat_project", "pat_forward_batched",
     "pat_adjoint_batched", "pat_desc_check", "pat_tv_prox_noalloc", "pat_diag_sync_costs", "pat_solves_check",
-    "pat_plan_wait_limit",
+    "pat_plan_wait_limit", "pat_batch_resident",
 ]
 
 
@@ -93,6 +93,7 @@ def lib() -> ctypes.CDLL:
         "pat_batch_create": (ctypes.c_int, [pp, pp, i32, i32]),
         "pat_batch_create_ex": (ctypes.c_int, [pp, pp, i32, i32, i32, i32, ctypes.c_uint32]),
         "pat_batch_destroy": (None, [vp]),
+        "pat_batch_resident": (ctypes.c_int, [vp, ctypes.POINTER(i32)]),
         "pat_batch_forward": (ctypes.c_int, [vp, pp, pp, vp]),
         "pat_batch_adjoint": (ctypes.c_int, [vp, pp, pp, vp]),
         "pat_forward_batched": (ctypes.c_int, [pp, i32, pp, pp, vp]),
@@ -300,7 +301,9 @@ class Plan:
 
 
 class Batch:
-    """Many plans run together (one launch per pass over all instances)."""
+    """Many plans run together: one launch per pass over all instances, or,
+    with the default settings and 2D grids where that is estimated to be
+    faster, the resident solves of all instances side by side."""
 
     def __init__(self, plans: Sequence[Plan], chunk: int = 0, parts: int = 0, lanes: int = 0, fuse: bool = True,
                  stagger: bool = True):
@@ -308,7 +311,8 @@ class Batch:
         per size class (0: 2); lanes: streams (0: one per group; fewer:
         groups placed heaviest first on the least-loaded stream); fuse: 2D
         size classes of axes 128/256/512 share their launches; stagger: odd
-        groups start one pass after the first (see pat_batch_create_ex)."""
+        groups start one pass after the first (see pat_batch_create_ex).  Any
+        setting but the defaults asks for the launches it describes."""
         self.plans = list(plans)
         self._opts = (int(chunk), int(parts), int(lanes), bool(fuse), bool(stagger))
         arr = (ctypes.c_void_p * len(self.plans))(*[p.handle.value for p in self.plans])
@@ -318,6 +322,13 @@ class Batch:
                                          flags),
                "pat_batch_create_ex")
         self._h = h
+
+    @property
+    def resident(self) -> bool:
+        """Whether the time loops run as resident solves (pat_batch_resident)."""
+        yes = ctypes.c_int32()
+        _check(lib().pat_batch_resident(self._h, ctypes.byref(yes)), "pat_batch_resident")
+        return bool(yes.value)
 
     def close(self):
         if getattr(self, "_h", None) is not None and self._h.value:
@@ -368,7 +379,8 @@ class Batch:
 
     def set_tile(self, entry: dict, tile: Optional[int] = None, fpb: Optional[int] = None) -> None:
         """Apply one stored choice: a report entry (keys n, nt, lossy, dir,
-        pass, tile, fpb); ``tile`` / ``fpb`` override the entry's."""
+        pass, tile, fpb); ``tile`` / ``fpb`` override the entry's.  The batch
+        then runs by launches."""
         t = entry["tile"] if tile is None else tile
         f = entry.get("fpb", 1) if fpb is None else fpb
         _check(lib().pat_batch_set_tile(self._h, _i32x3(list(entry["n"])), int(entry["nt"]), int(entry["lossy"]),
@@ -382,7 +394,10 @@ class Batch:
         device architecture and this batch composition (size classes with
         their instance counts, grouping options) are applied without timing;
         otherwise the batch is timed and its report stored in the file.
-        Returns the report entries in force."""
+        Returns the report entries in force: none for a batch that runs as
+        resident solves, whose file entry is neither read nor written."""
+        if self.resident:
+            return []
         arch = _arch()
         key = self._batch_key()
         if cache and os.path.exists(cache):

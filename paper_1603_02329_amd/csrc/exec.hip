@@ -1143,7 +1143,8 @@ extern "C" int pat_batch_create_ex(pat_batch** out, pat_plan* const* plans, int3
   }
   // resident solves: the instances of each shape and physics, longest first,
   // go to the die with the least work so far
-  b->resident = resident_pays(plans, nb);
+  // (explicit settings ask for the launches that they shape)
+  b->resident = !chunk && !parts && !lanes && !flags && resident_pays(plans, nb);
   std::vector<size_t> off_list, off_ctl;
   if (b->resident) {
     struct Work {
@@ -1252,6 +1253,12 @@ extern "C" int pat_batch_create_ex(pat_batch** out, pat_plan* const* plans, int3
     return rc;
   }
   *out = b;
+  return PAT_OK;
+}
+
+extern "C" int pat_batch_resident(const pat_batch* b, int32_t* yes) {
+  if (!b || !yes) return PAT_EINVAL;
+  *yes = b->resident;
   return PAT_OK;
 }
 
@@ -1397,6 +1404,7 @@ extern "C" int pat_batch_autotune(pat_batch* b, int32_t reps, void* stream) {
   if (hipStreamSynchronize(st) != hipSuccess) return PAT_EHIP;
   for (auto& c : b->cls)
     if (hipStreamSynchronize(c.st) != hipSuccess) return PAT_EHIP;
+  if (b->resident) return PAT_OK;  // no pass is launched by itself
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) {
     if (e0) hipEventDestroy(e0);
@@ -1583,6 +1591,7 @@ extern "C" int pat_batch_set_tile(pat_batch* b, const int32_t n[3], int32_t nt, 
       }
     found = true;
   }
+  if (found) b->resident = false;  // the variant is for the launches
   return found ? PAT_OK : PAT_EINVAL;
 }
 

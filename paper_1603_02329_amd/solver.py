@@ -41,8 +41,9 @@ class Level:
     """One grid level: plan, measured data (device, (nt, ns) float32),
     lambda and step size.  H and H^T run eagerly on the plan, or with
     ``graphs`` through a one-instance batch whose time loop is replayed from
-    captured graphs (measured at 512^2: no faster; a single grid's passes
-    are bound by their own duration, not by the host's launches)."""
+    captured graphs (2D grids that run as resident solves either way: a
+    launch of the whole loop; elsewhere measured no faster, a single grid's
+    passes are bound by their own duration, not by the host's launches)."""
 
     def __init__(self, plan: Plan, data, lam: float, alpha: float, graphs: bool = False):
         self.plan, self.data, self.lam, self.alpha = plan, data, lam, alpha
