@@ -231,7 +231,8 @@ def main():
     ap.add_argument("--steps", type=int, default=2)
     ap.add_argument("--warmup", type=int, default=1)
     ap.add_argument("--workload", default="cfg4")
-    ap.add_argument("--chunk", type=int, default=64, help="graph chunk (steps per captured graph; 1 = eager)")
+    ap.add_argument("--chunk", type=int, default=0,
+                    help="graph chunk (steps per captured graph; 1: eager; 0: the library default)")
     ap.add_argument("--no-plain", action="store_true")
     ap.add_argument("--plain-steps", type=int, default=3, help="timed steps of the plain path (after 1 warm-up)")
     ap.add_argument("--no-cpu", action="store_true")
