@@ -10,6 +10,9 @@
 #include <vector>
 
 #include "pat_internal.h"
+#include "prox_plan.h"
+
+using namespace pat;
 
 namespace {
 
@@ -160,8 +163,6 @@ __global__ void k_prox_zero_b(ProxBatch b) {  // r and p_prev of every image
 // 135 and 30 us, 512^2 175 and 35, 1024^2 372 and 95; 16 of 512^2 with 16 of
 // 256^2 2.01 and 0.46 ms.  Rows per wavefront at 512^2, 1024^2: two 45, 121
 // us, three 35, 95, four 42, 99.
-constexpr int kProxWaves = 16, kProxRows = 3, kProxH = kProxWaves * kProxRows;
-
 struct ProxImage {
   int n0, n1;
   const float* z;
@@ -559,31 +560,18 @@ ProxSteps prox_steps(const std::vector<float>& th, int k0, int k) {
   s.k = k;
   s.first = k0 == 0;
   s.last = k0 + k == (int)th.size();
-  s.tx = 64 - 2 * k - s.last;
-  s.ty = kProxH - 2 * k - s.last;
+  s.tx = prox_keep_x(k, s.last);
+  s.ty = prox_keep_y(k, s.last);
   std::copy_n(th.begin() + k0, k, s.theta);
   return s;
 }
-int prox_tiles(const Grid3& g, const ProxSteps& s) {
-  return ((g.n[0] + s.tx - 1) / s.tx) * ((g.n[1] + s.ty - 1) / s.ty);
-}
+int prox_blocks(const Grid3& g, const ProxSteps& s) { return (int)prox_tiles(g.n[0], g.n[1], s.tx, s.ty); }
 bool disjoint(const float* a, const float* b, long n) { return !a || !b || a + n <= b || b + n <= a; }
-// Whether launches of several iterations can run the image: they read z and
-// lower around a point that another workgroup may already have written to x.
+// Whether launches of several iterations can run the image (whether they pay:
+// ProxCost): they read z and lower around a point that another workgroup may
+// already have written to x.
 bool prox_windows(const Grid3& g, int ndim, const float* z, const float* lower, const float* x) {
   return ndim == 2 && disjoint(x, z, g.N) && disjoint(x, lower, g.N);
-}
-
-// [0, k0) and [k1, n_iter) run in one launch each, [k0, k1) two launches an
-// iteration: the workspace holds one copy of r and p_prev, which launches of
-// several iterations cannot update in place.  Up to 12 iterations one launch
-// is faster than two (14 iterations at 512^2: 31.9 us in one, 27.8 in two);
-// in halves a launch may take up to 16 (30 iterations: 67 us; 111 with at
-// most 12 and the rest two launches an iteration).
-constexpr int kProxOne = 12, kProxHalf = 16;
-void prox_split(int n_iter, int& k0, int& k1) {
-  k0 = n_iter <= kProxOne ? n_iter : std::min(kProxHalf, (n_iter + 1) / 2);
-  k1 = std::max(k0, n_iter - kProxHalf);
 }
 
 }  // namespace
@@ -627,6 +615,7 @@ extern "C" int pat_tv_prox_batched(int32_t count, int32_t ndim, const int32_t* n
     b.count = (int)std::min<size_t>(kProxBatch, iter.size() - i0);
     b.ndim = ndim;
     bool windows = true;
+    ProxCost cost(n_iter);
     for (int j = 0; j < b.count; ++j) {
       const int k = iter[i0 + j];
       make_grid(ndim, n + 3 * k, b.g[j]);
@@ -637,6 +626,7 @@ extern "C" int pat_tv_prox_batched(int32_t count, int32_t ndim, const int32_t* n
       b.lam[j] = (float)lambda_eff[k];
       b.step[j] = (float)(1.0 / (4.0 * ndim * lambda_eff[k]));
       windows = windows && prox_windows(b.g[j], ndim, b.z[j], b.lower[j], b.x[j]);
+      cost.add(b.g[j].n[0], b.g[j].n[1]);
     }
     auto blocks = [&](auto&& of) {
       b.begin[0] = 0;
@@ -645,11 +635,11 @@ extern "C" int pat_tv_prox_batched(int32_t count, int32_t ndim, const int32_t* n
     };
     auto steps = [&](int from, int k) {
       const ProxSteps s = prox_steps(th, from, k);
-      const int nb = blocks([&](const Grid3& g) { return prox_tiles(g, s); });
+      const int nb = blocks([&](const Grid3& g) { return prox_blocks(g, s); });
       hipLaunchKernelGGL(k_prox_steps_b, dim3(nb), dim3(64 * kProxWaves), 0, st, b, s);
     };
     int k0 = 0, k1 = n_iter;  // the iterations with launches of their own
-    if (windows) {
+    if (windows && cost.windows_pay()) {
       prox_split(n_iter, k0, k1);
       if (k0 > 0) steps(0, k0);
     }
@@ -687,9 +677,11 @@ int tv_prox_run(const Grid3& g, int ndim, const float* z, float* x, double lambd
   const ProxImage im{g.n[0], g.n[1], z, lower, x, r, lam, step};
   auto steps = [&](int from, int k) {
     const ProxSteps s = prox_steps(th, from, k);
-    hipLaunchKernelGGL(k_prox_steps, dim3(prox_tiles(g, s)), dim3(64 * kProxWaves), 0, st, im, s);
+    hipLaunchKernelGGL(k_prox_steps, dim3(prox_blocks(g, s)), dim3(64 * kProxWaves), 0, st, im, s);
   };
-  if (prox_windows(g, ndim, z, lower, x)) {
+  ProxCost cost(n_iter);
+  cost.add(g.n[0], g.n[1]);
+  if (prox_windows(g, ndim, z, lower, x) && cost.windows_pay()) {
     prox_split(n_iter, k0, k1);
     if (k0 > 0) steps(0, k0);
   }
