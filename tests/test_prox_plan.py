@@ -36,3 +36,20 @@ def test_thin_images_bitwise(shape, n_iter):
     small = torch.from_numpy(rng.standard_normal((40, 50)).astype(np.float32)).cuda()
     got = pat.tv_prox_batched([z, small], [0.3, 0.2], n_iter, lowers=[lower, None])
     assert torch.equal(got[0], both) and torch.equal(got[1], pat.tv_prox(small, 0.2, n_iter))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [(1, 1), (1, 3), (4, 1), (7, 9)])
+def test_step_beyond_float_bitwise(shape):
+    """lambda > 0 whose step 1 / (8 lambda) is infinite in float32: a point
+    without neighbours keeps max(z, lower)."""
+    torch = pytest.importorskip("torch")
+    import paper_1603_02329_amd as pat
+    z = torch.linspace(0.25, 2.0, shape[0] * shape[1]).reshape(shape).cuda()
+    zero = torch.zeros_like(z)
+    pat.tv_prox(z, 1e-40, 3, lower=zero, out=zero)
+    if z.numel() == 1:
+        assert torch.equal(zero, z)
+    got = pat.tv_prox(z, 1e-40, 3)
+    assert torch.equal(got.view(torch.int32), zero.view(torch.int32))
+    assert torch.equal(pat.tv_prox_batched([z], [1e-40], 3)[0].view(torch.int32), zero.view(torch.int32))
