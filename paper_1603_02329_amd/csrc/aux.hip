@@ -566,13 +566,16 @@ ProxSteps prox_steps(const std::vector<float>& th, int k0, int k) {
   return s;
 }
 int prox_blocks(const Grid3& g, const ProxSteps& s) { return (int)prox_tiles(g.n[0], g.n[1], s.tx, s.ty); }
-bool disjoint(const float* a, const float* b, long n) { return !a || !b || a + n <= b || b + n <= a; }
+bool disjoint(const float* a, long na, const float* b, long nb) { return !a || !b || a + na <= b || b + nb <= a; }
 // Whether launches of several iterations can run the image (whether they pay:
 // ProxCost): they read z and lower around a point that another workgroup may
-// already have written to x.  A step that overflowed makes NaN of the zeros
-// outside the image, which the windows read and the two launches do not.
-bool prox_windows(const Grid3& g, int ndim, const float* z, const float* lower, const float* x, float step) {
-  return ndim == 2 && std::isfinite(step) && disjoint(x, z, g.N) && disjoint(x, lower, g.N);
+// already have written to x; r and p_prev (work) likewise.  A step that
+// overflowed makes NaN of the zeros outside the image, which the windows read
+// and the two launches do not.
+bool prox_windows(const Grid3& g, int ndim, const float* z, const float* lower, const float* x, const float* work,
+                  float step) {
+  return ndim == 2 && std::isfinite(step) && disjoint(x, g.N, z, g.N) && disjoint(x, g.N, lower, g.N) &&
+         disjoint(x, g.N, work, 4 * g.N);
 }
 
 }  // namespace
@@ -626,7 +629,7 @@ extern "C" int pat_tv_prox_batched(int32_t count, int32_t ndim, const int32_t* n
       b.r[j] = (float*)work[k];
       b.lam[j] = (float)lambda_eff[k];
       b.step[j] = (float)(1.0 / (4.0 * ndim * lambda_eff[k]));
-      windows = windows && prox_windows(b.g[j], ndim, b.z[j], b.lower[j], b.x[j], b.step[j]);
+      windows = windows && prox_windows(b.g[j], ndim, b.z[j], b.lower[j], b.x[j], b.r[j], b.step[j]);
       cost.add(b.g[j].n[0], b.g[j].n[1]);
     }
     auto blocks = [&](auto&& of) {
@@ -682,7 +685,7 @@ int tv_prox_run(const Grid3& g, int ndim, const float* z, float* x, double lambd
   };
   ProxCost cost(n_iter);
   cost.add(g.n[0], g.n[1]);
-  if (prox_windows(g, ndim, z, lower, x, step) && cost.windows_pay()) {
+  if (prox_windows(g, ndim, z, lower, x, r, step) && cost.windows_pay()) {
     prox_split(n_iter, k0, k1);
     if (k0 > 0) steps(0, k0);
   }

@@ -53,3 +53,21 @@ def test_step_beyond_float_bitwise(shape):
     got = pat.tv_prox(z, 1e-40, 3)
     assert torch.equal(got.view(torch.int32), zero.view(torch.int32))
     assert torch.equal(pat.tv_prox_batched([z], [1e-40], 3)[0].view(torch.int32), zero.view(torch.int32))
+
+
+@pytest.mark.gpu
+def test_result_in_the_workspace_bitwise():
+    """The result may lie where the workspace's dual iterate does: nothing
+    reads that once the result is written."""
+    torch = pytest.importorskip("torch")
+    import paper_1603_02329_amd as pat
+    shape = (120, 200)
+    z = torch.from_numpy(np.random.default_rng(3).standard_normal(shape).astype(np.float32)).cuda()
+    for n_iter in (5, 20, 40):
+        ref = pat.tv_prox(z, 0.3, n_iter)
+        work = torch.empty(5 * z.numel(), device="cuda")
+        out = work[:z.numel()].view(shape)
+        pat.tv_prox(z, 0.3, n_iter, out=out, work=work.view(torch.uint8))
+        assert torch.equal(out, ref)
+        pat.tv_prox_batched([z], [0.3], n_iter, outs=[out], works=[work.view(torch.uint8)])
+        assert torch.equal(out, ref)
