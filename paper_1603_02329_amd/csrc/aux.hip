@@ -542,27 +542,26 @@ int red_buffer(hipStream_t st, double** out) {
   return PAT_OK;
 }
 
-// Extrapolation factors of n_iter FGP iterations.
-std::vector<float> fgp_thetas(int n_iter) {
-  std::vector<float> th(n_iter);
+// Extrapolation factors of the FGP iterations, one after another.
+struct FgpMomentum {
   double t = 1.0;
-  for (int k = 0; k < n_iter; ++k) {
+  float next() {
     const double tn = (1.0 + std::sqrt(1.0 + 4.0 * t * t)) / 2.0;
-    th[k] = (float)((t - 1.0) / tn);
+    const float theta = (float)((t - 1.0) / tn);
     t = tn;
+    return theta;
   }
-  return th;
-}
+};
 
 // Iterations [k0, k0 + k) of n_iter in one launch, the last of them all the way to x.
-ProxSteps prox_steps(const std::vector<float>& th, int k0, int k) {
+ProxSteps prox_steps(FgpMomentum& m, int k0, int k, int n_iter) {
   ProxSteps s{};
   s.k = k;
   s.first = k0 == 0;
-  s.last = k0 + k == (int)th.size();
+  s.last = k0 + k == n_iter;
   s.tx = prox_keep_x(k, s.last);
   s.ty = prox_keep_y(k, s.last);
-  std::copy_n(th.begin() + k0, k, s.theta);
+  for (int i = 0; i < k; ++i) s.theta[i] = m.next();
   return s;
 }
 int prox_blocks(const Grid3& g, const ProxSteps& s) { return (int)prox_tiles(g.n[0], g.n[1], s.tx, s.ty); }
@@ -613,7 +612,6 @@ extern "C" int pat_tv_prox_batched(int32_t count, int32_t ndim, const int32_t* n
       if (rc) return rc;
     }
   }
-  const std::vector<float> th = fgp_thetas(n_iter);
   for (size_t i0 = 0; i0 < iter.size(); i0 += kProxBatch) {
     ProxBatch b{};
     b.count = (int)std::min<size_t>(kProxBatch, iter.size() - i0);
@@ -637,8 +635,9 @@ extern "C" int pat_tv_prox_batched(int32_t count, int32_t ndim, const int32_t* n
       for (int j = 0; j < b.count; ++j) b.begin[j + 1] = b.begin[j] + of(b.g[j]);
       return b.begin[b.count];
     };
+    FgpMomentum mom;
     auto steps = [&](int from, int k) {
-      const ProxSteps s = prox_steps(th, from, k);
+      const ProxSteps s = prox_steps(mom, from, k, n_iter);
       const int nb = blocks([&](const Grid3& g) { return prox_blocks(g, s); });
       hipLaunchKernelGGL(k_prox_steps_b, dim3(nb), dim3(64 * kProxWaves), 0, st, b, s);
     };
@@ -650,8 +649,9 @@ extern "C" int pat_tv_prox_batched(int32_t count, int32_t ndim, const int32_t* n
     const int nb = blocks([](const Grid3& g) { return blocks_for(g.N); });
     if (k0 == 0) hipLaunchKernelGGL(k_prox_zero_b, dim3(nb), dim3(256), 0, st, b);
     for (int it = k0; it < k1; ++it) {
+      const float theta = mom.next();
       hipLaunchKernelGGL(k_prox_primal_b, dim3(nb), dim3(256), 0, st, b, 0);
-      hipLaunchKernelGGL(k_prox_dual_b, dim3(nb), dim3(256), 0, st, b, th[it]);
+      hipLaunchKernelGGL(k_prox_dual_b, dim3(nb), dim3(256), 0, st, b, theta);
     }
     if (k1 < n_iter) steps(k1, n_iter - k1);
     else if (k0 < n_iter) hipLaunchKernelGGL(k_prox_primal_b, dim3(nb), dim3(256), 0, st, b, 1);
@@ -676,11 +676,11 @@ int tv_prox_run(const Grid3& g, int ndim, const float* z, float* x, double lambd
   float* xt = pprev + (long)ndim * g.N;
   const float lam = (float)lambda_eff;
   const float step = (float)(1.0 / (4.0 * ndim * lambda_eff));
-  const std::vector<float> th = fgp_thetas(n_iter);
+  FgpMomentum mom;
   int k0 = 0, k1 = n_iter;  // the iterations with launches of their own
   const ProxImage im{g.n[0], g.n[1], z, lower, x, r, lam, step};
   auto steps = [&](int from, int k) {
-    const ProxSteps s = prox_steps(th, from, k);
+    const ProxSteps s = prox_steps(mom, from, k, n_iter);
     hipLaunchKernelGGL(k_prox_steps, dim3(prox_blocks(g, s)), dim3(64 * kProxWaves), 0, st, im, s);
   };
   ProxCost cost(n_iter);
@@ -691,8 +691,9 @@ int tv_prox_run(const Grid3& g, int ndim, const float* z, float* x, double lambd
   }
   if (k0 == 0) hipLaunchKernelGGL(k_zero, dim3(blocks_for(2L * ndim * g.N)), dim3(256), 0, st, 2L * ndim * g.N, r);
   for (int k = k0; k < k1; ++k) {
+    const float theta = mom.next();
     hipLaunchKernelGGL(k_prox_primal, dim3(nb), dim3(256), 0, st, g, ndim, z, lower, r, lam, xt);
-    hipLaunchKernelGGL(k_prox_dual, dim3(nb), dim3(256), 0, st, g, ndim, xt, step, th[k], r, pprev);
+    hipLaunchKernelGGL(k_prox_dual, dim3(nb), dim3(256), 0, st, g, ndim, xt, step, theta, r, pprev);
   }
   if (k1 < n_iter) steps(k1, n_iter - k1);
   else if (k0 < n_iter) hipLaunchKernelGGL(k_prox_primal, dim3(nb), dim3(256), 0, st, g, ndim, z, lower, pprev, lam, x);
