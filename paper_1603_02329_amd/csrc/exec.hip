@@ -479,7 +479,8 @@ int solve_one(const pat_plan* p, int dir, int s0, int s1, hipStream_t st) {
 
 // the time loop of one plan: steps [s0, s1) of direction dir
 int run_one(const pat_plan* p, const Runner& R, int dir, int s0, int s1, hipStream_t st) {
-  if (dir < 2 && resident(p) && !timing_on()) return solve_one(p, dir, s0, s1, st);
+  if (dir < 2 && resident(p) && solve_pays(p->hp.n[0], p->hp.n[1], s1 - s0) && !timing_on())
+    return solve_one(p, dir, s0, s1, st);
   return R.steps(dir, s0, s1, st);
 }
 

@@ -2,12 +2,10 @@
 #pragma once
 
 #include "pat_internal.h"
+#include "solve_rule.h"
 
 namespace pat {
 
-constexpr int kSolveXcds = 8;        // MI355X: 8 accelerator complex dies (XCDs), one L2 each
-constexpr int kSolveCus = 32;        // compute units per die
-constexpr int kSolveDomains = 16;    // most domains per die
 constexpr int kSolveQueue = 32768;   // most instances of a queue (16 bits hold a claim)
 constexpr int kSolveSpin = 1 << 24;  // polls after which a wait gives up (seconds), if not set otherwise
 constexpr uint32_t kSolveClosed = 0x80000000u;
@@ -17,35 +15,6 @@ constexpr uint32_t kSolveClosed = 0x80000000u;
 // ends after half a second in any case (before the others give up on it).
 constexpr uint64_t kSolveRollTicks = 50000000;
 constexpr uint32_t solve_ticks(long steps) { return steps > 10000 ? 25000000u : (uint32_t)(2500 * steps); }
-
-// Grids above this run on one domain over every die, the others on one die.
-// Per step (forward, lossy), on one die and over all: 256^2 22.9 and 25.8 us;
-// 512 x 128 22.3 and 24.9; 128 x 512 24.7 and 28.5; 512 x 256 50.2 and 31.5,
-// 512^2 87.6 and 39.5 (both before the barrier's words were spread).
-constexpr int kSolveDiePoints = 65536;
-constexpr bool solve_whole(int nx, int ny) { return nx * ny > kSolveDiePoints; }
-// Rows and columns are carried by two lanes where the per-launch passes have
-// one (PairStage): 4 values per lane; 8 for columns of 512 points, which would
-// not fit one wavefront otherwise.
-constexpr bool solve_pair_col(int ny) { return ny <= 256; }
-// rows of nx points that one wavefront carries
-constexpr int solve_rows(int nx) { return 512 / nx; }
-// wavefronts that a row pass of both parts can use
-constexpr int solve_waves(int nx, int ny) { return 2 * (ny / solve_rows(nx)); }
-// compute units of a domain
-constexpr int solve_cus(int nx, int ny) { return kSolveCus * (solve_whole(nx, ny) ? kSolveXcds : 1); }
-// wavefronts per member: two at least (the two parts of a tile exchange
-// through LDS), more once the tiles fill every compute unit
-constexpr int solve_nw(int nx, int ny) {
-  int nw = 2;
-  while (nw < 8 && nw * solve_cus(nx, ny) < solve_waves(nx, ny)) nw *= 2;
-  return nw;
-}
-// members the tiles keep busy, at most one per compute unit
-constexpr int solve_members(int nx, int ny) {
-  const int m = solve_waves(nx, ny) / solve_nw(nx, ny), cap = solve_cus(nx, ny);
-  return m < 1 ? 1 : m < cap ? m : cap;
-}
 
 // One domain: its roll, the instance its first member claimed, and the
 // barrier's words: one per die, each on a line of its own (over every die:
@@ -91,10 +60,6 @@ constexpr uint32_t solve_share(int rank, int n) { return rank == 0 ? 0u - kSolve
 
 constexpr size_t solve_ctl_bytes(int domains) { return sizeof(SolveCtl) + sizeof(SolveDom) * kSolveXcds * domains; }
 
-// whether there is a resident kernel for the grid
-inline bool solve_shape(int ndim, int nx, int ny) {
-  return ndim == 2 && nx >= 32 && nx <= 512 && ny >= 32 && ny <= 512;
-}
 // clears the control block, marks the instances as open (open: the kBadOpen
 // word of the one instance when there is no list) and runs the queue's time
 // loops, all of one shape
