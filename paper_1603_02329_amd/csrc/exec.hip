@@ -408,50 +408,6 @@ bool timing_on() {
 }
 bool resident(const pat_plan* p) { return solve_shape(p->desc.ndim, p->hp.n[0], p->hp.n[1]); }
 
-// Whether a batch runs as resident solves: when their estimated time is below
-// that of the batched launches (microseconds, forward, lossy; measured from
-// one to 64 instances of 64^2 to 512^2).  A resident step takes
-// 11.5 us + 0.17 us per 1000 points on its die, the dies working side by side
-// and each holding 32 / members domains; over every die 20.5 us + 0.053 us
-// per 1000 points, one instance at a time.  The instances over every die and
-// those on one run side by side too, at 0.4 of the shorter part's time.  A
-// step of the batched launches takes 42 us + 0.02 us per 1000 points of all
-// its instances; 54 us where classes of several shapes share their launches
-// (512^2 with 256^2 60 us, 4 of 128^2 with 4 of 256^2 65 us); 30 us and more
-// for each class where they do not (8 of 256^2 with 8 of 64^2 104 us, 6 each
-// of 128^2, 128 x 64 and 64^2 91 us).
-bool resident_pays(pat_plan* const* plans, int nb) {
-  double die[kSolveXcds] = {}, whole = 0, longest = 0, work = 0, steps_max = 1, steps_sum = 0;
-  std::vector<double> cost;  // time on a die, by the share of it that the instance holds
-  std::map<std::tuple<int, int, int>, int> classes;
-  bool shared = true;
-  if (nb > kSolveQueue) return false;
-  for (int i = 0; i < nb; ++i) {
-    const pat_plan* p = plans[i];
-    if (!resident(p)) return false;
-    const int nx = p->hp.n[0], ny = p->hp.n[1];
-    const double steps = std::max(0, p->desc.nt - 1), kpts = 1e-3 * (double)p->npoints;
-    shared = shared && fused_size(nx) && fused_size(ny);
-    if (classes.emplace(std::make_tuple(nx, ny, (int)p->desc.nt), i).second) steps_sum += steps;
-    steps_max = std::max(steps_max, steps);
-    work += steps * kpts;
-    if (solve_whole(nx, ny)) {
-      whole += steps * (20.5 + 0.053 * kpts);
-    } else {
-      const double t = steps * (11.5 + 0.17 * kpts);
-      longest = std::max(longest, t);
-      cost.push_back(t * solve_members(nx, ny) / kSolveCus);
-    }
-  }
-  std::sort(cost.rbegin(), cost.rend());
-  for (double c : cost) *std::min_element(die, die + kSolveXcds) += c;
-  const double dies = std::max(longest, *std::max_element(die, die + kSolveXcds));
-  const double t_res = std::max(whole, dies) + 0.4 * std::min(whole, dies);
-  double launches = steps_max * 42.0;
-  if (classes.size() > 1) launches = shared ? steps_max * 54.0 : std::max(launches, steps_sum * 30.0);
-  return t_res < launches + 0.02 * work;
-}
-
 SolveArgs solve_args(void* ctl, int domains) {
   SolveArgs a{};
   a.ctl = (SolveCtl*)ctl;
@@ -944,6 +900,8 @@ extern "C" int pat_batch_create_ex(pat_batch** out, pat_plan* const* plans, int3
   const int split = parts ? parts : 2;
   std::vector<std::vector<int>> groups;
   std::vector<int> group_fused;
+  std::vector<int> group_set;  // groups of one value are the parts of the same classes
+  int nsets = 0;
   {
     std::map<std::tuple<int, int, int, int, int, int>, int> key2grp;
     std::vector<std::vector<int>> shape_groups;
@@ -991,8 +949,10 @@ extern "C" int pat_batch_create_ex(pat_batch** out, pat_plan* const* plans, int3
         if (!g.empty()) {
           groups.push_back(g);
           group_fused.push_back(1);
+          group_set.push_back(nsets);
         }
       }
+      ++nsets;
       for (int s : fs) shape_groups[s].clear();
     }
     for (auto& g : shape_groups) {
@@ -1001,7 +961,9 @@ extern "C" int pat_batch_create_ex(pat_batch** out, pat_plan* const* plans, int3
       for (size_t k = 0; k < parts; ++k) {
         groups.emplace_back(g.begin() + g.size() * k / parts, g.begin() + g.size() * (k + 1) / parts);
         group_fused.push_back(0);
+        group_set.push_back(nsets);
       }
+      ++nsets;
     }
   }
   for (size_t gi = 0; gi < groups.size(); ++gi) {
@@ -1145,7 +1107,21 @@ extern "C" int pat_batch_create_ex(pat_batch** out, pat_plan* const* plans, int3
   // resident solves: the instances of each shape and physics, longest first,
   // go to the die with the least work so far
   // (explicit settings ask for the launches that they shape)
-  b->resident = !chunk && !parts && !lanes && !flags && resident_pays(plans, nb);
+  b->resident = !chunk && !parts && !lanes && !flags && nb <= kSolveQueue;
+  BatchCost cost;
+  for (int i = 0; i < nb && b->resident; ++i) {
+    const pat_plan* p = plans[i];
+    b->resident = resident(p);
+    if (b->resident) cost.instance(p->hp.n[0], p->hp.n[1], p->desc.nt - 1, p->lossy != 0);
+  }
+  for (size_t k = 0; k < b->cls.size(); ++k) {
+    if (std::find(group_set.begin(), group_set.begin() + k, group_set[k]) != group_set.begin() + k) continue;
+    long steps = 0;  // the parts of a set step side by side
+    for (size_t i = k; i < b->cls.size(); ++i)
+      if (group_set[i] == group_set[k]) steps = std::max(steps, (long)b->cls[i].nt - 1);
+    cost.set(steps, b->cls[k].lossy != 0, b->cls[k].fused != 0);
+  }
+  b->resident = b->resident && cost.resident_pays();
   std::vector<size_t> off_list, off_ctl;
   if (b->resident) {
     struct Work {
@@ -1181,7 +1157,7 @@ extern "C" int pat_batch_create_ex(pat_batch** out, pat_plan* const* plans, int3
         deep = std::max(deep, (int)q.order[x].size());
       }
       q.members = solve_members(q.nx, q.ny);
-      q.domains = solve_whole(q.nx, q.ny) ? 1 : std::max(1, std::min({deep, kSolveDomains, kSolveCus / q.members}));
+      q.domains = solve_domains(q.nx, q.ny, deep);
       off_list.push_back(take(sizeof(DevPlan*) * work.size()));
       off_ctl.push_back(take(solve_ctl_bytes(q.domains)));
     }
