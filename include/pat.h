@@ -532,7 +532,9 @@ int pat_project(int64_t n, const float* x, const float* lower, float* out, void*
  * PAT_EHIP if a resident solve gave up waiting for its own workgroups (a solve
  * of 2D grids whose workgroups meet at barriers; a wait is given up after
  * seconds).  The result of such a call, of every instance of a batch that did
- * not come to its end, is NaN throughout, and so are the later samples of a
+ * not come to its end, is NaN throughout, and so is everything that
+ * pat_forward, pat_adjoint and pat_forward_range and their batches give for the
+ * plan until a sync or check has reported it, and the later samples of a
  * pat_forward_range sequence.  When both happened, PAT_EHIP is reported and the
  * finite flag stays for the next sync.
  *

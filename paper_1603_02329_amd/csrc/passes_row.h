@@ -199,9 +199,10 @@ __device__ __forceinline__ void check_finite(const DevPlan& P, float2 v) {
   if ((P.flags & PAT_CHECK_FINITE) && !(isfinite(v.x) && isfinite(v.y))) atomicOr(P.bad + kBadFlags, kFlagNonFinite);
 }
 
-// whether the resident solve before this pass gave up (the flag is raised then)
+// whether the resident solve before this pass gave up (the flag is raised
+// then), or an earlier one did that nobody has asked about yet
 __device__ __forceinline__ bool unfinished(const DevPlan& P) {
-  const bool open = gld(P.bad, kBadOpen) != 0;
+  const bool open = gld(P.bad, kBadOpen) != 0 || (gld(P.bad, kBadFlags) & kFlagGaveUp) != 0;
   if (open && threadIdx.x == 0) atomicOr(P.bad + kBadFlags, kFlagGaveUp);
   return open;
 }

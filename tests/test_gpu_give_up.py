@@ -138,3 +138,39 @@ def test_solver_raises(run):
             solver.fista_batched([level], [p0], 2)
         else:
             solver.power_iteration(plan, p0, 2)
+
+
+@pytest.mark.parametrize("run", ["fista", "coarse", "batched"])
+def test_solver_raises_when_only_the_adjoint_gave_up(run):
+    """The prox makes zeros of a NaN image; the objective after it does not."""
+    plan, p0, h = _case(31, n=(64, 64), nt=9, ns=7, pml=6, lossy=True)
+
+    class OneBadAdjoint(solver.Level):
+        def adjoint(self, r):
+            self.plan.wait_limit(1)
+            g = super().adjoint(r)
+            self.plan.wait_limit(0)
+            return g
+
+    level = OneBadAdjoint(plan, h, 1e-3, 0.05)
+    with pytest.raises(pat.PatError) as e:
+        if run == "fista":
+            solver.fista(level, p0, 1)
+        elif run == "coarse":
+            solver.coarse_fista(level, p0, torch.zeros_like(p0), torch.zeros_like(p0), 1e-2, 1, 1e-2)
+        else:
+            level.adjoint(h)
+            solver.fista_batched([level], [p0], 1)
+    assert e.value.code == pat.PAT_EHIP
+    assert torch.isfinite(plan.forward(p0)).all()
+
+
+def test_results_stay_nan_until_asked():
+    plan, p0, h = _case(32, n=(512, 256), nt=6, ns=7, pml=6, lossy=False)
+    ref = plan.forward(p0).clone()
+    plan.wait_limit(1)
+    plan.adjoint(h)
+    plan.wait_limit(0)
+    assert torch.isnan(plan.forward(p0)).all() and torch.isnan(plan.adjoint(h)).all()
+    _raises_once(plan)
+    assert torch.equal(plan.forward(p0), ref)
