@@ -10,8 +10,10 @@
 // owns it.  No cache is written back or invalidated between passes: an
 // agent-scope release or acquire fence costs 15-20 us with 256 workgroups
 // running (every wavefront's write-back and invalidate queue up at the L2);
-// this barrier costs about 0.6 us within a die and 1.5-1.9 us over all eight.  A
-// pass of its own launch costs 5.5-9 us at 64^2 to 512^2, whatever the grid.
+// this barrier alone, in a build whose passes do nothing else, costs 0.40 us
+// with the 8 members of 64^2, 0.65 us with 32 members on a die and 1.5 us over
+// all eight.  A pass of its own launch costs 5.5-9 us at 64^2 to 512^2, whatever
+// the grid.
 //
 // Tiles are cut for latency: four values per lane (eight for columns of 512
 // points), the two parts of every pass (axis components, absorption terms, or
@@ -19,17 +21,18 @@
 // so that no wavefront runs more than two transforms between two barriers,
 // and as few wavefronts per compute unit as there are compute units for.
 // What bounds it is the chain of one wavefront: some 4 cycles per
-// instruction, four exchanges per transform, and the barrier (stores complete
-// after 0.27 us, a load from the L2 takes 0.09 us).  So what does not change
+// instruction, four exchanges per transform (4000-4500 of the 6100 cycles of a
+// pass at 128^2), and the barrier (stores complete after 0.27 us, a load from
+// the L2 takes 0.09 us).  So what does not change
 // through the time loop is not formed in it (the columns' multipliers stay in
 // registers), and the loads of a pass's own rows stand between the two halves
 // of the barrier.
 //
-// Per step of the time loop, launches, resident, and resident with these two
-// and the barrier's words on lines of their own (us): lossless forward 64^2
-// 22.5, 10.7, 8.8; lossy forward 64^2 32.9, 15.3, 12.5, 128^2 36.7, 20.8,
-// 15.3, 256 x 64 40.6, 20.0, 15.0, 256^2 43.9, 28.9, 22.9, 512^2 53.7, 39.8,
-// 34.3; the adjoint within 5% of the forward.
+// Per step of the time loop, launches, resident without these two, and as it
+// is, the barrier's words on lines of their own too (us): lossless forward 64^2
+// 22.5, 10.7, 8.4; lossy forward 64^2 32.9, 15.3, 12.5, 128^2 36.7, 20.8,
+// 15.2, 256 x 64 40.6, 20.0, 15.0, 256^2 43.9, 28.9, 23.3, 512^2 53.7, 39.8,
+// 34.5; the adjoint within 5% of the forward.
 //
 // Membership is dynamic, so that a domain never waits for a workgroup that
 // is not running: a domain's roll is closed when it is complete or after a

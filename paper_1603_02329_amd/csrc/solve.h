@@ -18,10 +18,11 @@ constexpr uint32_t solve_ticks(long steps) { return steps > 10000 ? 25000000u : 
 
 // One domain: its roll, the instance its first member claimed, and the
 // barrier's words: one per die, each on a line of its own (over every die:
-// in every die's entry), and one per member, two on a line.  (Words on one line queue up at the L2 when all are stored
-// and polled at once.  Per step, the members' words 32, 8, 2 and 1 on a line:
-// 128^2 17.6, 16.2, 15.3, 15.0 us, 256^2 26.1, 24.0, 23.1, 23.5; the dies'
-// words 8 and 1 on a line: 512^2 38.3 and 36.0.)
+// in every die's entry), and one per member, two on a line.  (Words on one line
+// queue up at the L2 when all are stored and polled at once.  Per step, when the
+// layout was chosen, the members' words 32, 8, 2 and 1 on a line: 128^2 17.6,
+// 16.2, 15.3, 15.0 us, 256^2 26.1, 24.0, 23.1, 23.5; then the dies' words 8 and
+// 1 on a line: 512^2 38.3 and 36.0.)
 constexpr int kSolveLine = 32;  // words
 constexpr int kSolveFlagLines = 16;
 constexpr int solve_flag(int member) {

@@ -13,9 +13,9 @@ constexpr int kSolveCus = 32;        // compute units per die
 constexpr int kSolveDomains = 16;    // most domains per die
 
 // Grids above this run on one domain over every die, the others on one die.
-// Per step (forward, lossy), on one die and over all: 256^2 22.9 and 25.8 us;
-// 512 x 128 22.3 and 24.9; 128 x 512 24.7 and 28.5; 512 x 256 50.2 and 31.5,
-// 512^2 87.6 and 39.5 (both before the barrier's words were spread).
+// Per step (forward, lossy, calls of 400 steps), on one die and over all: 256^2
+// 24.3 and 25.3 us; 512 x 128 24.0 and 24.1; 128 x 512 25.8 and 28.0; 512 x 256
+// 46.7 and 26.7; 256 x 512 43.9 and 30.8; 512^2 80.9 and 33.5.
 constexpr int kSolveDiePoints = 65536;
 constexpr bool solve_whole(int nx, int ny) { return nx * ny > kSolveDiePoints; }
 // Rows and columns are carried by two lanes where the per-launch passes have
